@@ -14,15 +14,20 @@ namespace {
 
 constexpr int kGroupM = 8;  // tile-rows walked together by the raster
 
-template <typename T, int BM, int BN, bool VEC_OK, int WGM, int WGN, int BKM, bool TA, bool TB>
-__global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS)) void gemm_native_kernel(
+// The FP64 128x128 tile on 8 wavefronts is held to 128 registers (6 spilled
+// outside the k loop): two workgroups per CU cover each other's barriers
+// (4 tiles per CU: 57.7 -> 59.8 TFLOP/s).
+template <typename T, int BM, int BN, int WGM, int WGN, int BKM, bool TA, bool TB>
+__global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS),
+                             (BM * BN == 128 * 128 && WGM * WGN == 8 && BKM == 1 ? 4
+                                                                                 : 1)) void gemm_native_kernel(
     GemmArgs<T> g, int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T *smem = reinterpret_cast<T *>(lds_raw);
   int tm, tn;
   const int t = xcd_remap(blockIdx.x, tiles_m * tiles_n);
   grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
-  gemm_tile<T, BM, BN, VEC_OK, WGM, WGN, BKM, TA, TB>(g, tm * BM, tn * BN, smem);
+  gemm_tile<T, BM, BN, WGM, WGN, BKM, TA, TB>(g, tm * BM, tn * BN, smem);
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1>
@@ -80,7 +85,7 @@ hipError_t set_max_lds(K kern, size_t bytes) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <typename T, int BM, int BN, bool VEC_OK, int WGM, int WGN, int BKM, bool TA, bool TB>
+template <typename T, int BM, int BN, int WGM, int WGN, int BKM, bool TA, bool TB>
 int launch_one(const GemmArgs<T> &g, hipStream_t s) {
   typedef TileShape<T, BM, BN, WGM, WGN, BKM, TA, TB> S;
   const int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
@@ -89,7 +94,7 @@ int launch_one(const GemmArgs<T> &g, hipStream_t s) {
     set_error("too many tiles (%lld) for one dispatch", (long long)tiles);
     return MG_ERR_INVALID_ARG;
   }
-  auto kern = gemm_native_kernel<T, BM, BN, VEC_OK, WGM, WGN, BKM, TA, TB>;
+  auto kern = gemm_native_kernel<T, BM, BN, WGM, WGN, BKM, TA, TB>;
   static const hipError_t attr = set_max_lds(kern, S::LDS_BYTES);  // once per instance
   MG_HIP_TRY(attr);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(S::THREADS), S::LDS_BYTES, s, g, tiles_m,
@@ -117,74 +122,74 @@ int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
 }
 
 // Work divisions 0-13 stage A and B through registers; 14-24 load them
-// straight into an LDS ring (16-byte aligned operands only: otherwise a
+// straight into an LDS ring (A and B 16-byte aligned only: otherwise a
 // register-staged division of the same macro-tile runs); 25 is the naive
 // one-output-per-lane mapping; 26-29 are direct-load rings whose wavefronts
 // form two k groups (twice the wavefronts per output block).  The host's table
 // of shapes (kCfgs in gemm_native.hip) lists the same divisions in order.
-template <typename T, bool V, bool TA, bool TB>
-int launch_cfg(int cfg, const GemmArgs<T> &g, hipStream_t s) {
+template <typename T, bool TA, bool TB>
+int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
   switch (cfg) {
-    case 0: return launch_one<T, 128, 128, V, 2, 2, 1, TA, TB>(g, s);
-    case 1: return launch_one<T, 128, 64, V, 2, 2, 1, TA, TB>(g, s);
-    case 2: return launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
-    case 3: return launch_one<T, 64, 32, V, 2, 2, 1, TA, TB>(g, s);
-    case 4: return launch_one<T, 32, 32, V, 2, 2, 1, TA, TB>(g, s);
-    case 5: return launch_one<T, 128, 128, V, 4, 2, 1, TA, TB>(g, s);
-    case 6: return launch_one<T, 128, 128, V, 2, 4, 1, TA, TB>(g, s);
-    case 7: return launch_one<T, 64, 64, V, 2, 2, 2, TA, TB>(g, s);
-    case 8: return launch_one<T, 128, 64, V, 4, 2, 1, TA, TB>(g, s);
-    case 9: return launch_one<T, 128, 64, V, 2, 2, 2, TA, TB>(g, s);
-    case 10: return launch_one<T, 256, 128, V, 4, 2, 1, TA, TB>(g, s);
-    case 11: return launch_one<T, 128, 256, V, 2, 4, 1, TA, TB>(g, s);
-    case 12: return launch_one<T, 256, 128, V, 4, 4, 1, TA, TB>(g, s);
-    case 13: return launch_one<T, 128, 128, V, 4, 2, 2, TA, TB>(g, s);
+    case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, s);
+    case 1: return launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
+    case 2: return launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+    case 3: return launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
+    case 4: return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, s);
+    case 5: return launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, s);
+    case 6: return launch_one<T, 128, 128, 2, 4, 1, TA, TB>(g, s);
+    case 7: return launch_one<T, 64, 64, 2, 2, 2, TA, TB>(g, s);
+    case 8: return launch_one<T, 128, 64, 4, 2, 1, TA, TB>(g, s);
+    case 9: return launch_one<T, 128, 64, 2, 2, 2, TA, TB>(g, s);
+    case 10: return launch_one<T, 256, 128, 4, 2, 1, TA, TB>(g, s);
+    case 11: return launch_one<T, 128, 256, 2, 4, 1, TA, TB>(g, s);
+    case 12: return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
+    case 13: return launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 14:
-      return V ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, s)
-               : launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 15:
-      return V ? launch_dma<T, 64, 32, 2, 2, 4, TA, TB>(g, s)
-               : launch_one<T, 64, 32, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 4, TA, TB>(g, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
     case 16:
-      return V ? launch_dma<T, 128, 64, 2, 2, 4, TA, TB>(g, s)
-               : launch_one<T, 128, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 4, TA, TB>(g, s)
+                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
     case 17:
-      return V ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, s)
-               : launch_one<T, 128, 128, V, 4, 2, 2, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, s)
+                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 18:
-      return V ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, s)
-               : launch_one<T, 256, 128, V, 4, 4, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, s)
+                    : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
     case 19:
-      return V ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, s)
-               : launch_one<T, 32, 32, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, s)
+                    : launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, s);
     case 20:
-      return V ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, s)
-               : launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 21:
-      return V ? launch_dma<T, 128, 128, 2, 4, 2, TA, TB>(g, s)
-               : launch_one<T, 128, 128, V, 4, 2, 2, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 2, TA, TB>(g, s)
+                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 22:
-      return V ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, s)
-               : launch_one<T, 128, 128, V, 4, 2, 2, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, s)
+                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 23:
-      return V ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB>(g, s)
-               : launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB>(g, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 24:
-      return V ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, s)
-               : launch_one<T, 64, 32, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
     case 25: return launch_naive<T, TA, TB>(g, s);
     case 26:
-      return V ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2>(g, s)
-               : launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2>(g, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 27:
-      return V ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, s)
-               : launch_one<T, 128, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, s)
+                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
     case 28:
-      return V ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, s)
-               : launch_one<T, 64, 64, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 29:
-      return V ? launch_dma<T, 64, 32, 2, 1, 2, TA, TB, 2>(g, s)
-               : launch_one<T, 64, 32, V, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 1, 2, TA, TB, 2>(g, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
   }
   set_error("unknown tile cfg %d", cfg);
   return MG_ERR_INVALID_ARG;
@@ -207,9 +212,8 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
   g.alpha = (T)alpha;
   g.beta = (T)beta;
   constexpr int VEC = Mfma<T>::VEC;
-  const bool vec_ok = vec_aligned(A, lda, sizeof(T), VEC) &&
-                      vec_aligned(B, ldb, sizeof(T), VEC) && vec_aligned(C, ldc, sizeof(T), VEC);
-  return vec_ok ? launch_cfg<T, true, TA, TB>(cfg, g, s) : launch_cfg<T, false, TA, TB>(cfg, g, s);
+  const bool dma_ok = vec_aligned(A, lda, sizeof(T), VEC) && vec_aligned(B, ldb, sizeof(T), VEC);
+  return launch_cfg<T, TA, TB>(cfg, dma_ok, g, s);
 }
 
 }  // namespace

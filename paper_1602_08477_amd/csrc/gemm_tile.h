@@ -9,8 +9,14 @@
 //   block   -> workgroup of 256 lanes = 4 wavefronts in a 2 x 2 arrangement
 //   thread  -> lane; its registers hold (BM/32)*(BN/32) MFMA accumulators
 //   element -> 16x16 MFMA fragments (4 values per lane) and 16-byte loads
-// A and B are double buffered in LDS: the global loads of k-tile t+1 are in
-// flight while the matrix cores work on tile t, with one barrier per tile.
+// A and B are double buffered in LDS with one barrier per k-tile, and the
+// global loads of the next PD k-tiles are in flight in registers.  With one
+// k-tile in flight and element-wise loads of rows that are not 16-byte
+// aligned this path was bound by memory latency and load count; 16-byte loads
+// at any address and PD = 4 (32x32 tiles) or 2 (64x64) gave, FP64 and FP32,
+// tightly packed odd extents: 1531 x 1033 x 2047 242 -> 169 us and 186 -> 87
+// us, 4095 x 4097 x 4099 4.04 -> 2.68 ms and 2.55 -> 1.42 ms; 384 x 384 x 8192
+// (A^T, aligned, 32x32 tiles, one per CU) 260 -> 175 us.
 //
 // LDS layouts (chosen for conflict-free 16-byte LDS traffic):
 //   A: [BK/VEC][BM+2][VEC]  -- VEC = 16/sizeof(T) consecutive k values of one
@@ -98,6 +104,10 @@ struct TileShape {
   static constexpr int B_STAGE = TB ? ACH * (BN + PA) * VEC : BK * (BN + PB);
   static constexpr int STAGE = A_STAGE + B_STAGE;
   static constexpr size_t LDS_BYTES = 2 * STAGE * sizeof(T);
+  // k-tiles in flight in registers: deep for the small tiles, whose k-tile is
+  // far shorter than a memory round trip; one where a k-tile's products cover
+  // it and the registers are needed for two workgroups per CU.
+  static constexpr int PD = NA + NB <= 2 ? 4 : NA + NB <= 4 && BM * BN <= 8192 ? 2 : 1;
   static_assert(WM % 16 == 0 && WN % 16 == 0 && FM >= 1 && FN >= 1, "wave tile of 16x16 blocks");
   static_assert(ACH <= 16 && 16 % ACH == 0, "A chunks per row");
   static_assert(NA >= 1 && NB >= 1 && A_CHUNKS % THREADS == 0 && B_CHUNKS % THREADS == 0,
@@ -105,19 +115,45 @@ struct TileShape {
   static_assert(ACH % 4 == 0, "k rounds of 4 lane groups");
 };
 
-// Loads one 16-byte chunk of a row: `left` elements remain in the row from p.
-template <typename T, bool VEC_OK>
-__device__ __forceinline__ typename Mfma<T>::vec_t load_chunk(const T *p, bool ok, int left) {
+// A 16-byte chunk at any element address.  Global loads and stores of several
+// dwords need dword alignment only, so a row of any pitch and base moves in
+// 16-byte chunks: an element-by-element path for rows that are not 16-byte
+// aligned costs VEC times the load instructions behind per-lane branches.
+template <typename T>
+struct Chunk {
   typedef typename Mfma<T>::vec_t V;
+  typedef V __attribute__((aligned(sizeof(T)))) U;
+  __device__ static __forceinline__ V load(const T *p) { return *reinterpret_cast<const U *>(p); }
+  __device__ static __forceinline__ void store(T *p, V v) { *reinterpret_cast<U *>(p) = v; }
+};
+
+// Elements `s`, s+1, ... of chunk x, then zeros (s >= VEC: all zeros).
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::vec_t shift_chunk(typename Mfma<T>::vec_t x, int s) {
   constexpr int VEC = Mfma<T>::VEC;
-  V r = {};
-  if (VEC_OK && ok && left >= VEC) {
-    r = *reinterpret_cast<const V *>(p);
-  } else if (ok) {
+  typename Mfma<T>::vec_t r = x;
 #pragma unroll
-    for (int v = 0; v < VEC; ++v)
-      if (v < left) r[v] = p[v];
+  for (int b = 1; b < VEC; b *= 2) {
+    typename Mfma<T>::vec_t y = r;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      const T up = v + b < VEC ? r[v + b < VEC ? v + b : v] : T(0);
+      y[v] = (s & b) ? up : r[v];
+    }
+    r = y;
   }
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) r[v] = s >= VEC ? T(0) : r[v];
+  return r;
+}
+
+// One 16-byte chunk of a row shorter than a chunk: `left` elements from p.
+template <typename T>
+__device__ __forceinline__ typename Mfma<T>::vec_t load_short(const T *p, int left) {
+  typename Mfma<T>::vec_t r = {};
+#pragma unroll
+  for (int v = 0; v < Mfma<T>::VEC; ++v)
+    if (v < left) r[v] = p[v];
   return r;
 }
 
@@ -146,11 +182,12 @@ __device__ __forceinline__ int f64_out_row(int row0, int i, int gq, int r) {
 // store (and the extra registers stay at one block row's worth).
 // FP64: neighbouring lanes (same rows, columns c and c+1) swap one value each
 // so that each lane owns a 16-byte pair of adjacent columns of one row.
-template <typename T, bool VEC_OK>
+// VEC: C moves in those pairs, at any 8-byte address (FP64).
+template <typename T, bool VEC>
 struct Epilogue;
 
-template <bool VEC_OK>
-struct Epilogue<double, VEC_OK> {
+template <bool VEC>
+struct Epilogue<double, VEC> {
   template <int FM, int FN, int AM, int AN, bool PA = false>
   __device__ static __forceinline__ void store(const GemmArgs<double> &g,
                                                const d4v (&acc)[AM][AN], int row0, int col0,
@@ -180,8 +217,8 @@ struct Epilogue<double, VEC_OK> {
           c[jb][h] = d2v{0.0, 0.0};
           if (!use_c || row >= g.m) continue;
           const double *p = g.C + (int64_t)row * g.ldc + col;
-          if (VEC_OK && col + 1 < g.n) {
-            c[jb][h] = *reinterpret_cast<const d2v *>(p);
+          if (VEC && col + 1 < g.n) {
+            c[jb][h] = Chunk<double>::load(p);
           } else {
             if (col < g.n) c[jb][h][0] = p[0];
             if (col + 1 < g.n) c[jb][h][1] = p[1];
@@ -199,8 +236,8 @@ struct Epilogue<double, VEC_OK> {
           for (int e = 0; e < 2; ++e)
             o[e] = use_c ? fma(g.alpha, v[jb][h][e], g.beta * c[jb][h][e]) : g.alpha * v[jb][h][e];
           double *p = g.C + (int64_t)row * g.ldc + col;
-          if (VEC_OK && col + 1 < g.n) {
-            *reinterpret_cast<d2v *>(p) = o;
+          if (VEC && col + 1 < g.n) {
+            Chunk<double>::store(p, o);
           } else {
             if (col < g.n) p[0] = o[0];
             if (col + 1 < g.n) p[1] = o[1];
@@ -213,7 +250,8 @@ struct Epilogue<double, VEC_OK> {
 // Epilogue of the column-paired FP64 fragment layout: block columns 2p and
 // 2p+1 of a wave hold the even and odd columns of one 32-column span, so
 // lane l owns columns 32p + 2(l%16) and 32p + 2(l%16) + 1 of each of its rows:
-// one 16-byte C load and store per pair, no lane exchange.  C 16-byte aligned.
+// one 16-byte C load and store per pair (at any 8-byte address), no lane
+// exchange.
 template <int FM, int FN, int AM, int AN, bool PA = false>
 __device__ __forceinline__ void store_paired_f64(const GemmArgs<double> &g,
                                                  const d4v (&acc)[AM][AN], int row0, int col0,
@@ -233,7 +271,7 @@ __device__ __forceinline__ void store_paired_f64(const GemmArgs<double> &g,
         c[p][r] = d2v{0.0, 0.0};
         if (!use_c || row >= g.m) continue;
         const double *q = g.C + (int64_t)row * g.ldc + col;
-        if (col + 1 < g.n) c[p][r] = *reinterpret_cast<const d2v *>(q);
+        if (col + 1 < g.n) c[p][r] = Chunk<double>::load(q);
         else if (col < g.n) c[p][r][0] = q[0];
       }
 #pragma unroll
@@ -250,14 +288,14 @@ __device__ __forceinline__ void store_paired_f64(const GemmArgs<double> &g,
           o[e] = use_c ? fma(g.alpha, v, g.beta * c[p][r][e]) : g.alpha * v;
         }
         double *q = g.C + (int64_t)row * g.ldc + col;
-        if (col + 1 < g.n) *reinterpret_cast<d2v *>(q) = o;
+        if (col + 1 < g.n) Chunk<double>::store(q, o);
         else if (col < g.n) q[0] = o[0];
       }
   }
 }
 
-template <bool VEC_OK>
-struct Epilogue<float, VEC_OK> {
+template <bool VEC>
+struct Epilogue<float, VEC> {
   template <int FM, int FN, int AM, int AN>
   __device__ static __forceinline__ void store(const GemmArgs<float> &g,
                                                const f4v (&acc)[AM][AN], int row0, int col0,
@@ -288,116 +326,138 @@ struct Epilogue<float, VEC_OK> {
   }
 };
 
+// One operand's share of a k-tile, per thread: N 16-byte chunks at any element
+// alignment.  KC: the stored rows run along k (A, or stored B^T): chunk (i, j)
+// is k chunk j of tile row i.  Otherwise the stored rows are k rows (B, or
+// stored A^T): chunk (i, j) is columns j.. of k row i.  Rows past the matrix
+// read its last row and their outputs are never stored.  A chunk that would
+// run past a row's end is loaded from the row's last full chunk instead and
+// shifted into place by fix(), so every load is one 16-byte instruction
+// without lane branches; rows shorter than a chunk are read element by
+// element.  k past the problem is zeroed by fix().
+// PD k-tiles are in flight at once, k-tile kt in register set kt % PD.
+template <typename T, int EXT, int BK, int THREADS, bool KC, int PD>
+struct Panel {
+  typedef typename Mfma<T>::vec_t V;
+  static constexpr int VEC = Mfma<T>::VEC;
+  static constexpr int CH = (KC ? BK : EXT) / VEC;  // chunks per stored row of the tile
+  static constexpr int N = EXT * BK / VEC / THREADS;
+  const T *p[N];
+  V x[PD][N];
+
+  __device__ static __forceinline__ int row_of(int tid, int u) { return (tid + THREADS * u) / CH; }
+  __device__ static __forceinline__ int col_of(int tid, int u) {  // element within the row
+    return (tid + THREADS * u) % CH * VEC;
+  }
+  // `base`: the stored matrix; c0: the tile's first row / column of `ext`.
+  __device__ __forceinline__ void init(const T *base, int64_t ld, int c0, int ext, int tid) {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = row_of(tid, u), j = col_of(tid, u);
+      p[u] = KC ? base + (int64_t)min(c0 + i, ext - 1) * ld + j
+                : base + (int64_t)i * ld + max(min(c0 + j, ext - VEC), 0);
+    }
+  }
+  // k-tiles [0, whole_tiles) take one plain load per chunk.
+  __device__ static __forceinline__ int whole_tiles(int ext, int k) {
+    return KC || ext >= VEC ? k / BK : 0;
+  }
+  __device__ __forceinline__ void load(int64_t ld, int kt, int set) {
+    const int64_t step = KC ? kt * BK : (int64_t)(kt * BK) * ld;
+#pragma unroll
+    for (int u = 0; u < N; ++u) x[set][u] = Chunk<T>::load(p[u] + step);
+  }
+  __device__ __forceinline__ void load_tail(int64_t ld, int c0, int ext, int k, int kt, int tid,
+                                            int set) {
+    const int kbase = kt * BK;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = row_of(tid, u), j = col_of(tid, u);
+      const int64_t rows = KC ? 0 : (int64_t)(min(kbase + i, k - 1) - i) * ld;
+      if ((KC ? k : ext) < VEC)
+        x[set][u] = KC ? load_short<T>(p[u] + kbase, k - kbase - j)
+                       : load_short<T>(p[u] + rows + c0 + j, ext - c0 - j);
+      else
+        x[set][u] = Chunk<T>::load(p[u] + (KC ? min(kbase + j, k - VEC) - j : rows));
+    }
+  }
+  // Puts chunks loaded from a row's end in place and zeroes k past the problem.
+  __device__ __forceinline__ void fix(int c0, int ext, int k, int kt, int tid, int set) {
+    const int kbase = kt * BK;
+    const bool tail = kbase + BK > k;
+    if (KC ? tail && k >= VEC : c0 + EXT > ext && ext >= VEC) {
+      const int c1 = KC ? kbase : c0, end = (KC ? k : ext) - VEC;
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const int c = c1 + col_of(tid, u);
+        x[set][u] = shift_chunk<T>(x[set][u], c - min(c, end));
+      }
+    }
+    if (!KC && tail) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        const bool in = kbase + row_of(tid, u) < k;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) x[set][u][v] = in ? x[set][u][v] : T(0);
+      }
+    }
+  }
+  // LDS position of chunk u: [k chunk][EXT + PA][VEC] or [k row][EXT + PB].
+  template <int PA, int PB>
+  __device__ __forceinline__ void put(T *lds, int tid, int set) const {
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int i = row_of(tid, u), j = col_of(tid, u);
+      T *q = KC ? lds + (j / VEC * (EXT + PA) + i) * VEC : lds + i * (EXT + PB) + j;
+      *reinterpret_cast<V *>(q) = x[set][u];
+    }
+  }
+};
+
 // Computes the BM x BN tile of C whose top-left output is (m0, n0) of
 // C <- alpha*op(A)*op(B) + beta*C (op = transpose when TA / TB is set).
 // `smem` holds 2 stages of TileShape::STAGE elements.  All THREADS lanes of
 // the workgroup must call this together (it contains barriers).
-template <typename T, int BM, int BN, bool VEC_OK, int WGM = 2, int WGN = 2, int BKM = 1,
-          bool TA = false, bool TB = false>
+template <typename T, int BM, int BN, int WGM = 2, int WGN = 2, int BKM = 1, bool TA = false,
+          bool TB = false>
 __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, T *smem) {
   typedef TileShape<T, BM, BN, WGM, WGN, BKM, TA, TB> S;
   typedef Mfma<T> M;
   typedef typename M::vec_t V;
   typedef typename M::acc_t Acc;
   constexpr int VEC = S::VEC, BK = S::BK;
-  constexpr int ACH = S::ACH;    // k chunks per tile row of A (and of stored B^T)
-  constexpr int BCH = BN / VEC;  // n chunks per k row of B
-  constexpr int MCH = BM / VEC;  // m chunks per k row of stored A^T
+  constexpr int ACH = S::ACH;  // k chunks per tile row of A (and of stored B^T)
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WGN) * S::WM, wn0 = (wave % WGN) * S::WN;
   const int gq = lane >> 4, l16 = lane & 15;
 
-  // Per-thread global chunk coordinates (fixed across k-tiles).
-  // A: (a_i, a_j) = (tile row, k chunk); transposed: (k row, first m column).
-  const T *pa[S::NA];
-  bool a_ok[S::NA];
-  int a_i[S::NA], a_j[S::NA], a_left[S::NA];
-#pragma unroll
-  for (int u = 0; u < S::NA; ++u) {
-    const int q = tid + S::THREADS * u;
-    if constexpr (!TA) {
-      a_i[u] = q / ACH;
-      a_j[u] = q % ACH;
-      const int grow = m0 + a_i[u];
-      a_ok[u] = grow < g.m;
-      pa[u] = g.A + (int64_t)(a_ok[u] ? grow : 0) * g.lda + a_j[u] * VEC;
-    } else {
-      a_i[u] = q / MCH;
-      a_j[u] = (q % MCH) * VEC;
-      const int gcol = m0 + a_j[u];
-      a_ok[u] = gcol < g.m;
-      a_left[u] = g.m - gcol;
-      pa[u] = g.A + (int64_t)a_i[u] * g.lda + (a_ok[u] ? gcol : 0);
-    }
-  }
-  // B: (b_i, b_j) = (k row, first n column); transposed: (tile column, k chunk).
-  const T *pb[S::NB];
-  bool b_ok[S::NB];
-  int b_i[S::NB], b_j[S::NB], b_left[S::NB];
-#pragma unroll
-  for (int u = 0; u < S::NB; ++u) {
-    const int q = tid + S::THREADS * u;
-    if constexpr (!TB) {
-      b_i[u] = q / BCH;
-      b_j[u] = (q % BCH) * VEC;
-      const int gcol = n0 + b_j[u];
-      b_ok[u] = gcol < g.n;
-      b_left[u] = g.n - gcol;
-      pb[u] = g.B + (int64_t)b_i[u] * g.ldb + (b_ok[u] ? gcol : 0);
-    } else {
-      b_i[u] = q / ACH;
-      b_j[u] = q % ACH;
-      const int gcol = n0 + b_i[u];
-      b_ok[u] = gcol < g.n;
-      pb[u] = g.B + (int64_t)(b_ok[u] ? gcol : 0) * g.ldb + b_j[u] * VEC;
-    }
-  }
-
-  V ra[S::NA], rb[S::NB];
-  auto load_tiles = [&](int kt) {
-    const int kbase = kt * BK;
-#pragma unroll
-    for (int u = 0; u < S::NA; ++u) {
-      if constexpr (!TA) {
-        const int kk = kbase + a_j[u] * VEC;
-        ra[u] = load_chunk<T, VEC_OK>(pa[u] + kbase, a_ok[u], g.k - kk);
-      } else {
-        const int kr = kbase + a_i[u];
-        ra[u] = load_chunk<T, VEC_OK>(pa[u] + (int64_t)kbase * g.lda, a_ok[u] && kr < g.k,
-                                      a_left[u]);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < S::NB; ++u) {
-      if constexpr (!TB) {
-        const int kr = kbase + b_i[u];
-        rb[u] = load_chunk<T, VEC_OK>(pb[u] + (int64_t)kbase * g.ldb, b_ok[u] && kr < g.k,
-                                      b_left[u]);
-      } else {
-        const int kk = kbase + b_j[u] * VEC;
-        rb[u] = load_chunk<T, VEC_OK>(pb[u] + kbase, b_ok[u], g.k - kk);
-      }
+  constexpr int PD = S::PD;
+  Panel<T, BM, BK, S::THREADS, !TA, PD> pa;
+  Panel<T, BN, BK, S::THREADS, TB, PD> pb;
+  pa.init(g.A, g.lda, m0, g.m, tid);
+  pb.init(g.B, g.ldb, n0, g.n, tid);
+  const int KT = (g.k + BK - 1) / BK;
+  const int KW = min(pa.whole_tiles(g.m, g.k), pb.whole_tiles(g.n, g.k));
+  auto load_tiles = [&](int kt, int set) {  // kt < KW
+    pa.load(g.lda, kt, set);
+    pb.load(g.ldb, kt, set);
+  };
+  auto load_any = [&](int kt, int set) {
+    if (kt < KW) {
+      load_tiles(kt, set);
+    } else if (kt < KT) {
+      pa.load_tail(g.lda, m0, g.m, g.k, kt, tid, set);
+      pb.load_tail(g.ldb, n0, g.n, g.k, kt, tid, set);
     }
   };
-  auto store_tiles = [&](int stage) {
-    T *As = smem + stage * S::STAGE;
-    T *Bs = As + S::A_STAGE;
-#pragma unroll
-    for (int u = 0; u < S::NA; ++u) {
-      if constexpr (!TA)
-        *reinterpret_cast<V *>(As + (a_j[u] * (BM + S::PA) + a_i[u]) * VEC) = ra[u];
-      else
-        *reinterpret_cast<V *>(As + a_i[u] * (BM + S::PB) + a_j[u]) = ra[u];
-    }
-#pragma unroll
-    for (int u = 0; u < S::NB; ++u) {
-      if constexpr (!TB)
-        *reinterpret_cast<V *>(Bs + b_i[u] * (BN + S::PB) + b_j[u]) = rb[u];
-      else
-        *reinterpret_cast<V *>(Bs + (b_j[u] * (BN + S::PA) + b_i[u]) * VEC) = rb[u];
-    }
+  auto store_tiles = [&](int kt, int set) {
+    T *As = smem + (kt & 1) * S::STAGE;
+    pa.fix(m0, g.m, g.k, kt, tid, set);
+    pb.fix(n0, g.n, g.k, kt, tid, set);
+    pa.template put<S::PA, S::PB>(As, tid, set);
+    pb.template put<S::PA, S::PB>(As + S::A_STAGE, tid, set);
   };
 
   Acc acc[S::FM][S::FN];
@@ -406,19 +466,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
 #pragma unroll
     for (int j = 0; j < S::FN; ++j) acc[i][j] = Acc{};
 
-  const int KT = (g.k + BK - 1) / BK;
-  MG_LDS_POISON_STAGE(smem, 2 * S::STAGE * (int)sizeof(T));
-  if (KT > 0) {
-    load_tiles(0);
-    store_tiles(0);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int cur = kt & 1;
-    // the other buffer is refilled after this step's products
-    MG_LDS_POISON_STAGE(smem + (cur ^ 1) * S::STAGE, S::STAGE * (int)sizeof(T));
-    if (kt + 1 < KT) load_tiles(kt + 1);
-    const T *As = smem + cur * S::STAGE;
+  auto compute = [&](int kt) {
+    const T *As = smem + (kt & 1) * S::STAGE;
     const T *Bs = As + S::A_STAGE;
 #pragma unroll
     for (int r = 0; r < ACH / 4; ++r) {
@@ -456,11 +505,41 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
           for (int j = 0; j < S::FN; ++j) acc[i][j] = M::mma(a[i][v], b[j], acc[i][j]);
       }
     }
-    if (kt + 1 < KT) store_tiles(cur ^ 1);
-    __syncthreads();
+  };
+
+  MG_LDS_POISON_STAGE(smem, 2 * S::STAGE * (int)sizeof(T));
+#pragma unroll
+  for (int q = 0; q < PD; ++q) load_any(q, q);
+  store_tiles(0, 0);
+  load_any(PD, 0);
+  __syncthreads();
+  // Step kt puts k-tile kt+1 in the other buffer (its last readers are behind
+  // the barrier) and starts the loads of k-tile kt+1+PD.  Whole k-tiles run
+  // without branches around the loads, so waits count only older loads.
+  int kt = 0;
+  for (; kt + 2 * PD < KW; kt += PD) {
+#pragma unroll
+    for (int j = 0; j < PD; ++j) {
+      MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+      store_tiles(kt + j + 1, (j + 1) % PD);
+      load_tiles(kt + j + 1 + PD, (j + 1) % PD);
+      compute(kt + j);
+      __syncthreads();
+    }
+  }
+  for (; kt < KT; kt += PD) {
+#pragma unroll
+    for (int j = 0; j < PD; ++j) {
+      if (kt + j >= KT) break;
+      MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+      if (kt + j + 1 < KT) store_tiles(kt + j + 1, (j + 1) % PD);
+      load_any(kt + j + 1 + PD, (j + 1) % PD);
+      compute(kt + j);
+      __syncthreads();
+    }
   }
 
-  Epilogue<T, VEC_OK>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
+  Epilogue<T, true>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
 }
 
 }  // namespace mg

@@ -148,7 +148,7 @@ void one_shape(int n, int reps, hipStream_t s, bool first) {
   if (cfg == 4) {
     typedef mg::TileShape<double, 32, 32, 2, 2, 1> S;
     raw = [&, tm, tn] {
-      direct(mg::gemm_native_kernel<double, 32, 32, true, 2, 2, 1, false, false>,
+      direct(mg::gemm_native_kernel<double, 32, 32, 2, 2, 1, false, false>,
              dim3(tm * tn), S::THREADS, S::LDS_BYTES, g, tm, tn, s);
     };
   } else if (cfg == 19 || cfg == 23 || cfg == 21 || cfg == 26) {
