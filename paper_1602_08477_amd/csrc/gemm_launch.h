@@ -30,15 +30,16 @@ __global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS),
   gemm_tile<T, BM, BN, WGM, WGN, BKM, TA, TB>(g, tm * BM, tn * BN, smem);
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1>
-__global__ __launch_bounds__((DmaShape<T, BM, BN, WGM, WGN, NS, KS>::THREADS),
-                             (DmaShape<T, BM, BN, WGM, WGN, NS, KS>::MINW)) void gemm_dma_kernel(
+template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1,
+          int KU = 1>
+__global__ __launch_bounds__((DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::THREADS),
+                             (DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::MINW)) void gemm_dma_kernel(
     GemmArgs<T> g, int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) unsigned char lds[];
   int tm, tn;
   const int t = xcd_remap(blockIdx.x, tiles_m * tiles_n);
   grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
-  gemm_dma_tile<T, BM, BN, WGM, WGN, NS, TA, TB, KS>(g, tm * BM, tn * BN, lds);
+  gemm_dma_tile<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU>(g, tm * BM, tn * BN, lds);
 }
 
 // The textbook mapping without the paper's hierarchy below the thread: one
@@ -103,16 +104,17 @@ int launch_one(const GemmArgs<T> &g, hipStream_t s) {
   return MG_OK;
 }
 
-template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1>
+template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1,
+          int KU = 1>
 int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
-  typedef DmaShape<T, BM, BN, WGM, WGN, NS, KS> S;
+  typedef DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU> S;
   const int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
   const int64_t tiles = (int64_t)tiles_m * tiles_n;
   if (tiles * S::THREADS > (int64_t)UINT32_MAX) {  // 32-bit work-item count per dispatch
     set_error("too many tiles (%lld) for one dispatch", (long long)tiles);
     return MG_ERR_INVALID_ARG;
   }
-  auto kern = gemm_dma_kernel<T, BM, BN, WGM, WGN, NS, TA, TB, KS>;
+  auto kern = gemm_dma_kernel<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU>;
   static const hipError_t attr = set_max_lds(kern, S::LDS_BYTES);  // once per instance
   MG_HIP_TRY(attr);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(S::THREADS), S::LDS_BYTES, s, g, tiles_m,
@@ -122,13 +124,22 @@ int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
 }
 
 // Work divisions 0-13 stage A and B through registers; 14-24 load them
-// straight into an LDS ring (A and B 16-byte aligned only: otherwise a
-// register-staged division of the same macro-tile runs); 25 is the naive
+// straight into an LDS ring (A and B 16-byte aligned, pitches under 16 MiB:
+// otherwise a register-staged division of the same macro-tile runs); 25 is the naive
 // one-output-per-lane mapping; 26-29 are direct-load rings whose wavefronts
 // form two k groups (twice the wavefronts per output block).  The host's table
 // of shapes (kCfgs in gemm_native.hip) lists the same divisions in order.
 template <typename T, bool TA, bool TB>
 int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
+  // FP32 halves the matrix cores' time per k-step, so its 64x64 and 64x32
+  // rings meet every second k-step (4 tiles of 64x64 per CU: 104 -> 116
+  // TFLOP/s; FP64, where the deeper stage costs resident workgroups, 71 -> 66).
+  // The 128x128 ring (21): FP64 on 16 wavefronts of 32x32, whose fragments
+  // fit twice, 72.8 TFLOP/s at n = 4096 against 72.0 on 8 wavefronts of
+  // 64x32; FP32 on 8 with two k-steps per stage, 125.6 at n = 2048 against
+  // 122.8 on 16.
+  constexpr bool F64 = sizeof(T) == 8;
+  constexpr int KU32 = F64 ? 1 : 2;
   switch (cfg) {
     case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, s);
     case 1: return launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
@@ -166,20 +177,21 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
       return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 21:
-      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 2, TA, TB>(g, s)
+      return dma_ok ? (F64 ? launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, s)
+                           : launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, s))
                     : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 22:
       return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, s)
                     : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
     case 23:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB>(g, s)
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 1, KU32>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 24:
       return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, s)
                     : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
     case 25: return launch_naive<T, TA, TB>(g, s);
     case 26:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2>(g, s)
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2, 2>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 27:
       return dma_ok ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, s)
@@ -188,7 +200,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 29:
-      return dma_ok ? launch_dma<T, 64, 32, 2, 1, 2, TA, TB, 2>(g, s)
+      return dma_ok ? launch_dma<T, 64, 32, 2, 1, 2, TA, TB, 2, KU32>(g, s)
                     : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
   }
   set_error("unknown tile cfg %d", cfg);
@@ -212,7 +224,11 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
   g.alpha = (T)alpha;
   g.beta = (T)beta;
   constexpr int VEC = Mfma<T>::VEC;
-  const bool dma_ok = vec_aligned(A, lda, sizeof(T), VEC) && vec_aligned(B, ldb, sizeof(T), VEC);
+  // The rings address a tile's rows by 32-bit offsets: at most 255 pitches
+  // plus a row of the tile.
+  const int64_t max_ld = ((int64_t)1 << 24) / (int64_t)sizeof(T);
+  const bool dma_ok = vec_aligned(A, lda, sizeof(T), VEC) &&
+                      vec_aligned(B, ldb, sizeof(T), VEC) && lda < max_ld && ldb < max_ld;
   return launch_cfg<T, TA, TB>(cfg, dma_ok, g, s);
 }
 

@@ -72,7 +72,9 @@ int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads) {
     return MG_OK;
   }
   if (bk) *bk = kCfgs[cfg].bkm * (dtype == MG_F64 ? Mfma<double>::BK : Mfma<float>::BK);
-  if (threads) *threads = 64 * kCfgs[cfg].wgm * kCfgs[cfg].wgn * kCfgs[cfg].ks;
+  if (threads)
+    *threads = cfg == 21 && dtype == MG_F64 ? 1024  // 16 wavefronts (launch_cfg)
+                                            : 64 * kCfgs[cfg].wgm * kCfgs[cfg].wgn * kCfgs[cfg].ks;
   return MG_OK;
 }
 

@@ -56,3 +56,27 @@ def test_unaligned_edges(cfg, ta, tb, dt):
         outside = torch.ones_like(buf, dtype=torch.bool)
         outside[1:1 + m * ((n + 2) | 1)].view(m, -1)[:, :n] = False
         assert torch.equal(buf[outside], before[outside]), (m, n, k)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (1, 1)])
+def test_pitch_beyond_ring_offsets(ta, tb):
+    """16-byte aligned rows 16 MiB apart: past what the direct-load rings
+    address from a tile's corner, so a register-staged tile runs."""
+    m, n, k = 5, 6, 4
+    A, B, C = host_mats(synth.config_seed(1, 71), m, n, k)
+    ld = (1 << 21) + 2
+
+    def far(x):
+        t = torch.full((x.shape[0], ld), float("nan"), dtype=torch.float64, device="cuda")
+        t[:, :x.shape[1]] = torch.from_numpy(np.ascontiguousarray(x))
+        return t[:, :x.shape[1]]
+
+    dA, dB = far(A.T if ta else A), far(B.T if tb else B)
+    ref = oracle.dgemm(1.5, A, B, 0.5, C)
+    bound = elementwise_bound(1.5, A, B, 0.5, C, k)
+    for cfg in (None, 19, 21, 23, 26):
+        log(f"far pitch cfg={cfg} ta={ta} tb={tb}")
+        dC = torch.from_numpy(C).cuda()
+        mg.gemm_ex(dA, dB, dC, 1.5, 0.5, transa=bool(ta), transb=bool(tb), cfg=cfg)
+        torch.cuda.synchronize()
+        assert (np.abs(dC.cpu().numpy() - ref) <= bound).all(), cfg
