@@ -19,8 +19,7 @@ constexpr int kGroupM = 8;  // tile-rows walked together by the raster
 // (4 tiles per CU: 57.7 -> 59.8 TFLOP/s).
 template <typename T, int BM, int BN, int WGM, int WGN, int BKM, bool TA, bool TB>
 __global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS),
-                             (BM * BN == 128 * 128 && WGM * WGN == 8 && BKM == 1 ? 4
-                                                                                 : 1)) void gemm_native_kernel(
+                             (TileShape<T, BM, BN, WGM, WGN, BKM>::MINW)) void gemm_native_kernel(
     GemmArgs<T> g, int tiles_m, int tiles_n) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T *smem = reinterpret_cast<T *>(lds_raw);
@@ -154,7 +153,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
     case 10: return launch_one<T, 256, 128, 4, 2, 1, TA, TB>(g, s);
     case 11: return launch_one<T, 128, 256, 2, 4, 1, TA, TB>(g, s);
     case 12: return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
-    case 13: return launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
+    case 13: return launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
     case 14:
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
@@ -166,7 +165,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
                     : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
     case 17:
       return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, s)
-                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
     case 18:
       return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, s)
                     : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
@@ -179,10 +178,10 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
     case 21:
       return dma_ok ? (F64 ? launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, s)
                            : launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, s))
-                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
     case 22:
       return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, s)
-                    : launch_one<T, 128, 128, 4, 2, 2, TA, TB>(g, s);
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
     case 23:
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 1, KU32>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);

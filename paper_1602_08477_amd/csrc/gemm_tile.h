@@ -16,7 +16,12 @@
 // at any address and PD = 4 (32x32 tiles) or 2 (64x64) gave, FP64 and FP32,
 // tightly packed odd extents: 1531 x 1033 x 2047 242 -> 169 us and 186 -> 87
 // us, 4095 x 4097 x 4099 4.04 -> 2.68 ms and 2.55 -> 1.42 ms; 384 x 384 x 8192
-// (A^T, aligned, 32x32 tiles, one per CU) 260 -> 175 us.
+// (A^T, aligned, 32x32 tiles, one per CU) 260 -> 175 us.  What was left was
+// the latency of the fragment reads and the barrier between two k-tiles:
+// with fragments read a round ahead (small wave tiles), FP64 at k = 2048 by
+// tiles per CU: 32x32 1: 24 -> 31, 12: 45 -> 49; 64x64 1: 42 -> 52, 4: 56 ->
+// 64, 12: 59 -> 67; 128x64 on 8 wavefronts 2: 60 -> 64; 128x128 64 -> 68
+// TFLOP/s.
 //
 // LDS layouts (chosen for conflict-free 16-byte LDS traffic):
 //   A: [BK/VEC][BM+2][VEC]  -- VEC = 16/sizeof(T) consecutive k values of one
@@ -108,6 +113,17 @@ struct TileShape {
   // far shorter than a memory round trip; one where a k-tile's products cover
   // it and the registers are needed for two workgroups per CU.
   static constexpr int PD = NA + NB <= 2 ? 4 : NA + NB <= 4 && BM * BN <= 8192 ? 2 : 1;
+  // Fragments read one round ahead.  Not the FP32 64x64 tile: the second set
+  // costs it a workgroup per CU (4 tiles per CU: 119 -> 112 TFLOP/s).
+  static constexpr bool AHEAD =
+      FM * FN <= 4 && !(sizeof(T) == 4 && FM * FN == 4 && THREADS == 256);
+  // Wavefronts per SIMD the registers must leave room for (the second
+  // __launch_bounds__ value): at one the compiler would keep the sums in
+  // accumulation registers and copy them every k-tile.
+  static constexpr int MINW = FM * FN * sizeof(T) >= 128  ? 1
+                              : AHEAD && BKM == 1         ? (FM * FN < 4 || THREADS >= 512 ? 4 : 3)
+                              : BM * BN == 128 * 128 && THREADS == 512 && BKM == 1 ? 4
+                                                                                   : 2;
   static_assert(WM % 16 == 0 && WN % 16 == 0 && FM >= 1 && FN >= 1, "wave tile of 16x16 blocks");
   static_assert(ACH <= 16 && 16 % ACH == 0, "A chunks per row");
   static_assert(NA >= 1 && NB >= 1 && A_CHUNKS % THREADS == 0 && B_CHUNKS % THREADS == 0,
@@ -326,6 +342,13 @@ struct Epilogue<float, VEC> {
   }
 };
 
+// Workgroup barrier after this wavefront's LDS accesses (lgkmcnt 0; loads in
+// flight stay in flight: vmcnt and expcnt at their maxima are not waited for).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  __builtin_amdgcn_s_barrier();
+}
+
 // One operand's share of a k-tile, per thread: N 16-byte chunks at any element
 // alignment.  KC: the stored rows run along k (A, or stored B^T): chunk (i, j)
 // is k chunk j of tile row i.  Otherwise the stored rows are k rows (B, or
@@ -381,11 +404,13 @@ struct Panel {
         x[set][u] = Chunk<T>::load(p[u] + (KC ? min(kbase + j, k - VEC) - j : rows));
     }
   }
-  // Puts chunks loaded from a row's end in place and zeroes k past the problem.
-  __device__ __forceinline__ void fix(int c0, int ext, int k, int kt, int tid, int set) {
+  // Puts chunks loaded from a row's end in place and zeroes k past the
+  // problem; `whole`: k-tiles that load() reads, where only columns past the
+  // matrix's edge matter.
+  __device__ __forceinline__ void fix(int c0, int ext, int k, int kt, int tid, int set,
+                                      bool whole) {
     const int kbase = kt * BK;
-    const bool tail = kbase + BK > k;
-    if (KC ? tail && k >= VEC : c0 + EXT > ext && ext >= VEC) {
+    if (KC ? !whole && k >= VEC : c0 + EXT > ext && ext >= VEC) {
       const int c1 = KC ? kbase : c0, end = (KC ? k : ext) - VEC;
 #pragma unroll
       for (int u = 0; u < N; ++u) {
@@ -393,7 +418,7 @@ struct Panel {
         x[set][u] = shift_chunk<T>(x[set][u], c - min(c, end));
       }
     }
-    if (!KC && tail) {
+    if (!KC && !whole) {
 #pragma unroll
       for (int u = 0; u < N; ++u) {
         const bool in = kbase + row_of(tid, u) < k;
@@ -452,10 +477,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
       pb.load_tail(g.ldb, n0, g.n, g.k, kt, tid, set);
     }
   };
-  auto store_tiles = [&](int kt, int set) {
-    T *As = smem + (kt & 1) * S::STAGE;
-    pa.fix(m0, g.m, g.k, kt, tid, set);
-    pb.fix(n0, g.n, g.k, kt, tid, set);
+  auto store_tiles = [&](int kt, int buf, int set, bool whole) {
+    T *As = smem + buf * S::STAGE;
+    pa.fix(m0, g.m, g.k, kt, tid, set, whole);
+    pb.fix(n0, g.n, g.k, kt, tid, set, whole);
     pa.template put<S::PA, S::PB>(As, tid, set);
     pb.template put<S::PA, S::PB>(As + S::A_STAGE, tid, set);
   };
@@ -466,76 +491,159 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
 #pragma unroll
     for (int j = 0; j < S::FN; ++j) acc[i][j] = Acc{};
 
-  auto compute = [&](int kt) {
-    const T *As = smem + (kt & 1) * S::STAGE;
+  // Fragments of one round (k chunks 4r + 0..3, one per lane group): VEC
+  // MFMAs per block.
+  struct Frag {
+    V a[S::FM];
+    T b[VEC][S::FN];
+  };
+  auto load_frag = [&](Frag &f, int buf, int r) {
+    const T *As = smem + buf * S::STAGE;
     const T *Bs = As + S::A_STAGE;
+    const int kc = 4 * r + gq;  // this lane group's chunk
 #pragma unroll
-    for (int r = 0; r < ACH / 4; ++r) {
-      const int kc = 4 * r + gq;  // this lane group's chunk
-      V a[S::FM];
+    for (int i = 0; i < S::FM; ++i) {
+      if constexpr (!TA) {
+        f.a[i] = *reinterpret_cast<const V *>(As + (kc * (BM + S::PA) + wm0 + 16 * i + l16) * VEC);
+      } else {
 #pragma unroll
-      for (int i = 0; i < S::FM; ++i) {
-        if constexpr (!TA) {
-          a[i] = *reinterpret_cast<const V *>(As + (kc * (BM + S::PA) + wm0 + 16 * i + l16) * VEC);
-        } else {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v)
-            a[i][v] = As[(kc * VEC + v) * (BM + S::PB) + wm0 + 16 * i + l16];
-        }
+        for (int v = 0; v < VEC; ++v)
+          f.a[i][v] = As[(kc * VEC + v) * (BM + S::PB) + wm0 + 16 * i + l16];
       }
-      V bv[S::FN];  // transposed B: one chunk of VEC k values per block column
-      if constexpr (TB) {
+    }
 #pragma unroll
-        for (int j = 0; j < S::FN; ++j)
-          bv[j] = *reinterpret_cast<const V *>(Bs + (kc * (BN + S::PA) + wn0 + 16 * j + l16) * VEC);
-      }
+    for (int j = 0; j < S::FN; ++j) {
+      if constexpr (TB) {  // transposed B: one chunk of VEC k values per block column
+        const V bv =
+            *reinterpret_cast<const V *>(Bs + (kc * (BN + S::PA) + wn0 + 16 * j + l16) * VEC);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        T b[S::FN];
+        for (int v = 0; v < VEC; ++v) f.b[v][j] = bv[v];
+      } else {
 #pragma unroll
-        for (int j = 0; j < S::FN; ++j) {
-          if constexpr (!TB)
-            b[j] = Bs[(kc * VEC + v) * (BN + S::PB) + wn0 + 16 * j + l16];
-          else
-            b[j] = bv[j][v];
-        }
-#pragma unroll
-        for (int i = 0; i < S::FM; ++i)
-#pragma unroll
-          for (int j = 0; j < S::FN; ++j) acc[i][j] = M::mma(a[i][v], b[j], acc[i][j]);
+        for (int v = 0; v < VEC; ++v)
+          f.b[v][j] = Bs[(kc * VEC + v) * (BN + S::PB) + wn0 + 16 * j + l16];
       }
     }
   };
+  auto mma_first = [&](const Frag &f) { acc[0][0] = M::mma(f.a[0][0], f.b[0][0], acc[0][0]); };
+  auto mma_rest = [&](const Frag &f) {
+#pragma unroll
+    for (int v = 0; v < VEC; ++v)
+#pragma unroll
+      for (int i = 0; i < S::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < S::FN; ++j)
+          if (v + i + j > 0) acc[i][j] = M::mma(f.a[i][v], f.b[v][j], acc[i][j]);
+  };
+  constexpr int U = ACH / 4;  // rounds per k-tile
 
   MG_LDS_POISON_STAGE(smem, 2 * S::STAGE * (int)sizeof(T));
 #pragma unroll
   for (int q = 0; q < PD; ++q) load_any(q, q);
-  store_tiles(0, 0);
+  store_tiles(0, 0, 0, KW > 0);
   load_any(PD, 0);
   __syncthreads();
-  // Step kt puts k-tile kt+1 in the other buffer (its last readers are behind
-  // the barrier) and starts the loads of k-tile kt+1+PD.  Whole k-tiles run
-  // without branches around the loads, so waits count only older loads.
   int kt = 0;
-  for (; kt + 2 * PD < KW; kt += PD) {
+  if constexpr (S::AHEAD) {
+    // Small wave tiles: a round's fragments are read from LDS while the
+    // matrix cores work on the previous round's.  In step kt, k-tile kt+1 goes
+    // to the other buffer (its last readers are behind the barrier) and the
+    // loads of k-tile kt+1+PD start; before the last round the wavefronts
+    // meet, with their LDS writes done and their fragments of k-tile kt in
+    // registers (products may be scheduled past the barrier, so they do not
+    // imply it).  The order is pinned: one product first, whose wait covers
+    // only this round's fragments, then what the others hide.
+    Frag f[2];
+    load_frag(f[0], 0, 0);
+    constexpr int UNR = PD > 1 ? PD : 2;  // buffers and register sets alternate
+    static_assert(UNR % 2 == 0 && UNR * U % 2 == 0, "constant LDS and fragment addresses");
+    for (; kt + UNR + PD < KW; kt += UNR) {
 #pragma unroll
-    for (int j = 0; j < PD; ++j) {
-      MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
-      store_tiles(kt + j + 1, (j + 1) % PD);
-      load_tiles(kt + j + 1 + PD, (j + 1) % PD);
-      compute(kt + j);
-      __syncthreads();
+      for (int j = 0; j < UNR; ++j)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const Frag &cur = f[(j * U + u) & 1];
+          Frag &nx = f[(j * U + u + 1) & 1];
+          if (u + 1 == U) {
+            lds_barrier();
+            mma_first(cur);
+            __builtin_amdgcn_sched_barrier(0);
+            load_frag(nx, (j + 1) & 1, 0);
+          } else {
+            mma_first(cur);
+            __builtin_amdgcn_sched_barrier(0);
+            load_frag(nx, j & 1, u + 1);
+            if (u == 0) {
+              MG_LDS_POISON_STAGE(smem + ((j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+              store_tiles(kt + j + 1, (j + 1) & 1, (j + 1) % PD, true);
+              load_tiles(kt + j + 1 + PD, (j + 1) % PD);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          mma_rest(cur);
+          __builtin_amdgcn_sched_barrier(0);
+        }
     }
-  }
-  for (; kt < KT; kt += PD) {
+    for (; kt < KT; kt += PD) {
 #pragma unroll
-    for (int j = 0; j < PD; ++j) {
-      if (kt + j >= KT) break;
-      MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
-      if (kt + j + 1 < KT) store_tiles(kt + j + 1, (j + 1) % PD);
-      load_any(kt + j + 1 + PD, (j + 1) % PD);
-      compute(kt + j);
-      __syncthreads();
+      for (int j = 0; j < PD; ++j) {
+        if (kt + j >= KT) break;
+        const int buf = (kt + j) & 1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (u + 1 == U) {
+            lds_barrier();
+            if (kt + j + 1 < KT) load_frag(f[1], buf ^ 1, 0);
+          } else {
+            load_frag(f[1], buf, u + 1);
+            if (u == 0) {
+              MG_LDS_POISON_STAGE(smem + (buf ^ 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+              if (kt + j + 1 < KT)
+                store_tiles(kt + j + 1, buf ^ 1, (j + 1) % PD, kt + j + 1 < KW);
+              load_any(kt + j + 1 + PD, (j + 1) % PD);
+            }
+          }
+          mma_first(f[0]);
+          mma_rest(f[0]);
+          f[0] = f[1];
+        }
+      }
+    }
+  } else {
+    // Step kt puts k-tile kt+1 in the other buffer (its last readers are
+    // behind the barrier) and starts the loads of k-tile kt+1+PD.  Whole
+    // k-tiles run without branches around the loads, so waits count only
+    // older loads.
+    auto compute = [&](int t) {
+      Frag f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        load_frag(f, t & 1, u);
+        mma_first(f);
+        mma_rest(f);
+      }
+    };
+    for (; kt + 2 * PD < KW; kt += PD) {
+#pragma unroll
+      for (int j = 0; j < PD; ++j) {
+        MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+        store_tiles(kt + j + 1, (kt + j + 1) & 1, (j + 1) % PD, true);
+        load_tiles(kt + j + 1 + PD, (j + 1) % PD);
+        compute(kt + j);
+        __syncthreads();
+      }
+    }
+    for (; kt < KT; kt += PD) {
+#pragma unroll
+      for (int j = 0; j < PD; ++j) {
+        if (kt + j >= KT) break;
+        MG_LDS_POISON_STAGE(smem + ((kt + j + 1) & 1) * S::STAGE, S::STAGE * (int)sizeof(T));
+        if (kt + j + 1 < KT)
+          store_tiles(kt + j + 1, (kt + j + 1) & 1, (j + 1) % PD, kt + j + 1 < KW);
+        load_any(kt + j + 1 + PD, (j + 1) % PD);
+        compute(kt + j);
+        __syncthreads();
+      }
     }
   }
 
