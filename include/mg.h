@@ -105,7 +105,10 @@ int mg_gemm_cfg(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alph
                 const void *A, int64_t lda, const void *B, int64_t ldb,
                 double beta, void *C, int64_t ldc, void *stream);
 
-/* The cfg mg_gemm picks for this shape (its work-division rule). */
+/* The cfg mg_gemm picks for this shape (its work-division rule) when A and B
+ * have 16-byte aligned rows and pitches under 16 MiB, which the direct-load
+ * rings need; for other operands it picks among the register-staged divisions
+ * by the same rule. */
 int mg_pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
 
 /* mg_gemm_ex: C <- alpha*op(A)*op(B) + beta*C on the native kernels, with

@@ -199,7 +199,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
     case 29:
-      return dma_ok ? launch_dma<T, 64, 32, 2, 1, 2, TA, TB, 2, KU32>(g, s)
+      return dma_ok ? launch_dma<T, 64, 32, 2, 1, F64 ? 2 : 3, TA, TB, 2, KU32>(g, s)
                     : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
   }
   set_error("unknown tile cfg %d", cfg);
@@ -222,12 +222,7 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
   g.k = (int)k;
   g.alpha = (T)alpha;
   g.beta = (T)beta;
-  constexpr int VEC = Mfma<T>::VEC;
-  // The rings address a tile's rows by 32-bit offsets: at most 255 pitches
-  // plus a row of the tile.
-  const int64_t max_ld = ((int64_t)1 << 24) / (int64_t)sizeof(T);
-  const bool dma_ok = vec_aligned(A, lda, sizeof(T), VEC) &&
-                      vec_aligned(B, ldb, sizeof(T), VEC) && lda < max_ld && ldb < max_ld;
+  const bool dma_ok = ring_operands(sizeof(T) == 8 ? MG_F64 : MG_F32, A, lda, B, ldb);
   return launch_cfg<T, TA, TB>(cfg, dma_ok, g, s);
 }
 

@@ -11,7 +11,14 @@ bool vec_aligned(const void *p, int64_t ld, int64_t esz, int vec);
 
 int num_tile_cfgs();
 int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads);
+// The division mg_gemm picks for operands the direct-load rings can load.
 int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
+// The same for either kind of operands (`ring`: ring_operands of A and B).
+int pick_division(int dtype, bool ring, int64_t m, int64_t n);
+// True if the direct-load rings can load A and B: 16-byte aligned rows, and
+// pitches whose tile offsets fit the rings' 32-bit lane offsets (255 pitches
+// plus a row of the tile).
+bool ring_operands(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
 
 // Enqueues C <- alpha*A*B + beta*C with work division `cfg` (arguments
 // already validated).

@@ -78,35 +78,98 @@ int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads) {
   return MG_OK;
 }
 
+bool ring_operands(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb) {
+  const int64_t esz = dtype == MG_F64 ? 8 : 4;
+  const int64_t max_ld = ((int64_t)1 << 24) / esz;
+  return vec_aligned(A, lda, esz, 16 / (int)esz) && vec_aligned(B, ldb, esz, 16 / (int)esz) &&
+         lda < max_ld && ldb < max_ld;
+}
+
+namespace {
+
+// Measured rate (TFLOP/s, whole chip, k = 2048) of a work division when every
+// CU has 1, 2, 3-5 and 6 or more of its tiles to run.  A tile takes as long
+// whether it is full or reaches past the matrix, and the CU with the most
+// tiles ends last, so a division's time is ceil(tiles / CUs) tiles at that
+// rate: 128x128 tiles are the fastest per flop, but n = 3000 gives some CUs
+// three of them and the others two (683 us by this count; 64x64 tiles: nine
+// on every CU, 520 us; measured 1092 -> 821 us).
+struct TileRate {
+  int cfg;
+  float r[4];
+};
+constexpr TileRate kRing64[] = {{21, {70.f, 71.3f, 72.f, 73.f}},
+                                {23, {64.4f, 67.4f, 70.5f, 71.3f}},
+                                {15, {59.2f, 63.3f, 65.5f, 66.5f}},
+                                {19, {48.f, 57.f, 60.f, 62.f}}};
+constexpr TileRate kRing32[] = {{22, {120.6f, 130.1f, 131.5f, 133.f}},
+                                {21, {126.f, 127.7f, 128.5f, 128.7f}},
+                                {23, {106.7f, 110.7f, 115.f, 119.f}},
+                                {15, {99.3f, 106.f, 107.f, 111.f}},
+                                {19, {85.8f, 98.5f, 102.5f, 109.f}}};
+// Operands the rings cannot load: the register-staged divisions.
+constexpr TileRate kReg64[] = {{5, {61.6f, 67.9f, 67.8f, 68.f}},
+                               {8, {58.f, 64.5f, 65.f, 66.f}},
+                               {2, {52.5f, 62.4f, 64.5f, 66.8f}},
+                               {3, {42.9f, 49.6f, 54.f, 55.3f}},
+                               {4, {30.7f, 42.8f, 47.f, 49.f}}};
+constexpr TileRate kReg32[] = {{5, {116.7f, 126.9f, 128.5f, 129.f}},
+                               {8, {110.7f, 117.f, 119.f, 121.f}},
+                               {2, {81.f, 103.f, 117.f, 124.f}},
+                               {3, {74.9f, 96.1f, 106.5f, 112.f}},
+                               {4, {56.1f, 80.2f, 91.f, 98.f}}};
+constexpr int64_t kCus = 256;
+
+// Flops per CU of `units` workgroups of one division, over its rate.
+double division_cost(const TileRate &t, int64_t units) {
+  const int64_t per_cu = ceil_div(units, kCus);
+  const float r = t.r[per_cu <= 1 ? 0 : per_cu == 2 ? 1 : per_cu <= 5 ? 2 : 3];
+  return (double)per_cu * kCfgs[t.cfg].bm * kCfgs[t.cfg].bn / r;
+}
+
+int64_t tiles_of(int cfg, int64_t m, int64_t n) {
+  return ceil_div(m, kCfgs[cfg].bm) * ceil_div(n, kCfgs[cfg].bn);
+}
+
+// 32x32 ring tiles only where an extent is below 1024: with both above, the
+// wide and tall panels they re-read twice as often as 64x32 tiles are large.
+template <size_t N>
+const TileRate *best_division(const TileRate (&rates)[N], int64_t m, int64_t n) {
+  const TileRate *best = nullptr;
+  double cost = 0;
+  for (const TileRate &t : rates) {
+    if (t.cfg == 19 && std::min(m, n) >= 1024) continue;
+    const double c = division_cost(t, tiles_of(t.cfg, m, n));
+    if (best == nullptr || c < cost) {
+      best = &t;
+      cost = c;
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
+int pick_division(int dtype, bool ring, int64_t m, int64_t n) {
+  const bool f64 = dtype != MG_F32;
+  if (!ring) return (f64 ? best_division(kReg64, m, n) : best_division(kReg32, m, n))->cfg;
+  const int cfg = (f64 ? best_division(kRing64, m, n) : best_division(kRing32, m, n))->cfg;
+  // Between 2^20 and 2^22 outputs the 64x64 and 64x32 tiles run as two k
+  // groups of wavefronts where those are as fast: 64x64 tiles that leave a CU
+  // at most one (two wavefronts per SIMD instead of one: within 3 % of the
+  // one-group ring either way), 64x32 tiles from four per CU (FP64 68 against
+  // 66.5 TFLOP/s).
+  const int64_t outputs = m * n;
+  if (outputs >= (int64_t)1 << 20 && outputs < (int64_t)1 << 22) {
+    if (cfg == 23 && tiles_of(23, m, n) <= kCus) return 26;
+    if (cfg == 15 && tiles_of(15, m, n) > 3 * kCus) return 29;
+  }
+  return cfg;
+}
+
 int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k) {
   (void)k;
-  // Measured on MI355X (16-byte aligned operands), FP64: the 128x128 ring on
-  // 8 wavefronts once it gives every CU two tiles (90 % of peak at 8192);
-  // below that the 64x64 ring on 4 wavefronts while it still gives every CU
-  // three or more tiles (n = 2048: 64.7 TFLOP/s against 64.1 for 128x128;
-  // n = 2560: 58.7 against 54.2); then the 64x32 ring with two k groups of
-  // wavefronts while it gives every CU four tiles (n = 1536: 49.9 against
-  // 44.6), the 64x64 one with two k groups (n = 1024: 44-47 against 41-43);
-  // then the 32x32 ring (n = 512).
-  // FP32: the 128x128 ring on 4 wavefronts from four tiles per CU, on 8
-  // from one, then the same smaller tiles.  Below those the small
-  // register-staged tiles; unaligned operands run a register-staged
-  // division of the same macro-tile.
-  auto tiles = [&](int c) { return ceil_div(m, kCfgs[c].bm) * ceil_div(n, kCfgs[c].bn); };
-  const int64_t cus = 256;
-  if (dtype == MG_F32) {
-    if (tiles(22) >= 4 * cus) return 22;
-    if (tiles(21) >= cus) return 21;
-  } else {
-    if (tiles(21) >= 2 * cus) return 21;
-    if (tiles(23) >= 3 * cus) return 23;
-    if (tiles(29) >= 4 * cus) return 29;
-  }
-  if (tiles(26) >= cus) return 26;
-  if (tiles(19) >= cus) return 19;
-  if (tiles(2) >= 2 * cus) return 2;
-  if (tiles(3) >= 2 * cus) return 3;
-  return 4;
+  return pick_division(dtype, true, m, n);
 }
 
 int gemm_tiles_nn(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha,

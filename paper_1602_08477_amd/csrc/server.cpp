@@ -180,8 +180,10 @@ void launch_batch(Server *S, Lane &L, int64_t batch_id) {
     if (q->r.algo == MG_NATIVE && rc != MG_OK) q->res.status = rc;
   for (Req *q : direct) {
     const mg_problem &p = q->r.p;
-    const int r2 = gemm_native(q->r.dtype, pick_tile_cfg(q->r.dtype, p.m, p.n, p.k), p.m, p.n,
-                               p.k, p.alpha, p.A, p.lda, p.B, p.ldb, p.beta, p.C, p.ldc, L.s);
+    const int cfg = pick_division(q->r.dtype, ring_operands(q->r.dtype, p.A, p.lda, p.B, p.ldb),
+                                  p.m, p.n);
+    const int r2 = gemm_native(q->r.dtype, cfg, p.m, p.n, p.k, p.alpha, p.A, p.lda, p.B, p.ldb,
+                               p.beta, p.C, p.ldc, L.s);
     if (r2 != MG_OK) q->res.status = r2;
   }
   // Split requests: one batched split launch set per algorithm (each result

@@ -80,3 +80,31 @@ def test_pitch_beyond_ring_offsets(ta, tb):
         mg.gemm_ex(dA, dB, dC, 1.5, 0.5, transa=bool(ta), transb=bool(tb), cfg=cfg)
         torch.cuda.synchronize()
         assert (np.abs(dC.cpu().numpy() - ref) <= bound).all(), cfg
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("pad", [1, 16])
+def test_picked_division_gives_the_same_bits(pad, dt):
+    """Shapes around the points where the work-division rule changes its
+    mind, for operands of both kinds: the picked division's result is the
+    32x32 register-staged tile's, bit for bit (one k group)."""
+    dtype = torch.float64 if dt == "f64" else torch.float32
+    for i, (m, n, k) in enumerate([(31, 33, 65), (511, 513, 96), (1023, 1009, 50), (777, 2053, 40),
+                                   (1531, 1033, 47), (2600, 700, 33), (3001, 2999, 35),
+                                   (4095, 4097, 17)]):
+        if pad > 1 and mg.pick_tile_cfg(m, n, k, mg.F64 if dt == "f64" else mg.F32) >= 26:
+            continue
+        log(f"pick {dt} pad={pad} {(m, n, k)}")
+        g = torch.Generator(device="cuda").manual_seed(100 + i)
+
+        def mat(r, c):
+            t = torch.empty(r, -(-c // pad) * pad + (pad == 1 and c % 2 == 0), dtype=dtype,
+                            device="cuda").uniform_(-1, 1, generator=g)
+            return t[:, :c]
+
+        A, B, C = mat(m, k), mat(k, n), mat(m, n)
+        one, two = C.clone(), C.clone()
+        mg.gemm(A, B, one, 1.5, 0.5)
+        mg.gemm(A, B, two, 1.5, 0.5, cfg=4)
+        torch.cuda.synchronize()
+        assert torch.equal(one, two), (m, n, k)
