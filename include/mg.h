@@ -12,7 +12,8 @@
  *    plain pointer plus extent plus pitch (Section 3.4, "Memory").
  *  - All matrix pointers are DEVICE pointers owned by the caller.  The library
  *    never allocates, frees, copies or migrates them (no implicit data
- *    movement, Section 3.1).  Host arrays of descriptors are read during the
+ *    movement, Section 3.1); workspaces it needs come from its own
+ *    stream-ordered pool where an entry point says so.  Host arrays of descriptors are read during the
  *    call only.
  *  - `stream` is a hipStream_t passed as void*; work is enqueued on it in
  *    order and the call returns without waiting (an asynchronous stream in the
@@ -78,7 +79,14 @@ int mg_build_flags(void);
  *   A,B,C  device pointers to dtype elements, naturally aligned.
  * The work division (macro-tile shape, i.e. blocks, threads per block and
  * elements per thread in the paper's terms, Table 2 and Section 3.4) is
- * chosen by the library from the shape.  The split algorithms use the
+ * chosen by the library from the shape.  With MG_NATIVE, a product with few
+ * output tiles and k >= 1024 may be cut along k over workgroups: each part
+ * sums its k range in the order of a one-k-group work division into a
+ * workspace (at most 64 MiB) from the library's stream-ordered pool, and a
+ * second kernel adds the parts in order (deterministic; within the rounding
+ * bound of the uncut sum, not its bits).  While `stream` is being captured, or
+ * if the pool cannot give the workspace, the product runs uncut.  The split
+ * algorithms use the
  * default slice count (mg_split_default_slices) and take their workspace
  * from the library's stream-ordered workspace pool on `stream` (released on
  * the same stream; see mg_release_cached_memory); use mg_gemm_split to
@@ -119,7 +127,7 @@ int mg_pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
  * plain layout (bit-identical results for the same cfg).
  *   transa 0: A stored m x k, lda >= k;  1: A stored k x m, lda >= m.
  *   transb 0: B stored k x n, ldb >= n;  1: B stored n x k, ldb >= k.
- *   cfg    a work division as in mg_gemm_cfg, or -1 for mg_pick_tile_cfg's.
+ *   cfg    a work division as in mg_gemm_cfg, or -1 for mg_gemm's choice.
  *   dtype  MG_F64 or MG_F32.  Other arguments, special cases and errors as
  *          mg_gemm (MG_ERR_INVALID_ARG for trans flags other than 0/1). */
 int mg_gemm_ex(int dtype, int cfg, int transa, int transb, int64_t m, int64_t n, int64_t k,
@@ -246,7 +254,8 @@ int mg_release_cached_memory(void);
  * division (26-29; FP64 and FP32 problems with roughly 2^20 <= m*n < 2^22,
  * e.g. n = 1024 and 1536): those add two half-sums per output at the end, so
  * there the batched and single results agree to the rounding bound
- * (k+2)u(|alpha||A||B| + |beta||C|) per element, not bit for bit.
+ * (k+2)u(|alpha||A||B| + |beta||C|) per element, not bit for bit; nor where
+ * mg_gemm cuts k (k >= 1024 with few output tiles).
  * Problems may share A and B; no C may overlap another problem's C, A or B
  * (checked on the byte spans [first element, last element], so interleaved
  * sub-blocks of one buffer are rejected).  dtype MG_F64 or MG_F32. */

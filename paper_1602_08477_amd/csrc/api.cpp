@@ -285,7 +285,9 @@ int mg_gemm_ex(int dtype, int cfg, int transa, int transb, int64_t m, int64_t n,
   int rc = validate_problem_op("gemm_ex", transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C,
                                ldc, es);
   if (rc != MG_OK) return rc;
-  if (cfg < 0) cfg = pick_division(dtype, ring_operands(dtype, A, lda, B, ldb), m, n);
+  if (cfg < 0)
+    return gemm_native_auto(dtype, transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
+                            static_cast<hipStream_t>(stream));
   return gemm_native_op(dtype, cfg, transa, transb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc,
                         static_cast<hipStream_t>(stream));
 }
@@ -347,8 +349,7 @@ int mg_gemm(int dtype, int algo, int64_t m, int64_t n, int64_t k, double alpha, 
   if (rc != MG_OK) return rc;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (algo == MG_NATIVE)
-    return gemm_native(dtype, pick_division(dtype, ring_operands(dtype, A, lda, B, ldb), m, n), m, n,
-                       k, alpha, A, lda, B, ldb, beta, C, ldc, s);
+    return gemm_native_auto(dtype, false, false, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
   return gemm_split_pooled(algo, split_default_slices(algo), m, n, k, alpha,
                            static_cast<const double *>(A), lda, static_cast<const double *>(B),
                            ldb, beta, static_cast<double *>(C), ldc, s);

@@ -20,11 +20,12 @@ constexpr int kGroupM = 8;  // tile-rows walked together by the raster
 template <typename T, int BM, int BN, int WGM, int WGN, int BKM, bool TA, bool TB>
 __global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS),
                              (TileShape<T, BM, BN, WGM, WGN, BKM>::MINW)) void gemm_native_kernel(
-    GemmArgs<T> g, int tiles_m, int tiles_n) {
+    GemmArgs<T> g, int tiles_m, int tiles_n, KSplit<T> ks) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   T *smem = reinterpret_cast<T *>(lds_raw);
   int tm, tn;
-  const int t = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+  const int tiles = tiles_m * tiles_n;
+  const int t = take_part<T, TA, TB>(g, ks, xcd_remap(blockIdx.x, tiles * ks.parts), tiles);
   grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
   gemm_tile<T, BM, BN, WGM, WGN, BKM, TA, TB>(g, tm * BM, tn * BN, smem);
 }
@@ -33,10 +34,11 @@ template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB
           int KU = 1>
 __global__ __launch_bounds__((DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::THREADS),
                              (DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::MINW)) void gemm_dma_kernel(
-    GemmArgs<T> g, int tiles_m, int tiles_n) {
+    GemmArgs<T> g, int tiles_m, int tiles_n, KSplit<T> ks) {
   extern __shared__ __align__(16) unsigned char lds[];
   int tm, tn;
-  const int t = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+  const int tiles = tiles_m * tiles_n;
+  const int t = take_part<T, TA, TB>(g, ks, xcd_remap(blockIdx.x, tiles * ks.parts), tiles);
   grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
   gemm_dma_tile<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU>(g, tm * BM, tn * BN, lds);
 }
@@ -86,10 +88,10 @@ hipError_t set_max_lds(K kern, size_t bytes) {
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int BKM, bool TA, bool TB>
-int launch_one(const GemmArgs<T> &g, hipStream_t s) {
+int launch_one(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
   typedef TileShape<T, BM, BN, WGM, WGN, BKM, TA, TB> S;
   const int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
-  const int64_t tiles = (int64_t)tiles_m * tiles_n;
+  const int64_t tiles = (int64_t)tiles_m * tiles_n * ks.parts;
   if (tiles * S::THREADS > (int64_t)UINT32_MAX) {  // 32-bit work-item count per dispatch
     set_error("too many tiles (%lld) for one dispatch", (long long)tiles);
     return MG_ERR_INVALID_ARG;
@@ -98,17 +100,17 @@ int launch_one(const GemmArgs<T> &g, hipStream_t s) {
   static const hipError_t attr = set_max_lds(kern, S::LDS_BYTES);  // once per instance
   MG_HIP_TRY(attr);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(S::THREADS), S::LDS_BYTES, s, g, tiles_m,
-                     tiles_n);
+                     tiles_n, ks);
   MG_HIP_TRY(hipGetLastError());
   return MG_OK;
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1,
           int KU = 1>
-int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
+int launch_dma(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
   typedef DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU> S;
   const int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
-  const int64_t tiles = (int64_t)tiles_m * tiles_n;
+  const int64_t tiles = (int64_t)tiles_m * tiles_n * ks.parts;
   if (tiles * S::THREADS > (int64_t)UINT32_MAX) {  // 32-bit work-item count per dispatch
     set_error("too many tiles (%lld) for one dispatch", (long long)tiles);
     return MG_ERR_INVALID_ARG;
@@ -117,7 +119,7 @@ int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
   static const hipError_t attr = set_max_lds(kern, S::LDS_BYTES);  // once per instance
   MG_HIP_TRY(attr);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(S::THREADS), S::LDS_BYTES, s, g, tiles_m,
-                     tiles_n);
+                     tiles_n, ks);
   MG_HIP_TRY(hipGetLastError());
   return MG_OK;
 }
@@ -129,7 +131,7 @@ int launch_dma(const GemmArgs<T> &g, hipStream_t s) {
 // form two k groups (twice the wavefronts per output block).  The host's table
 // of shapes (kCfgs in gemm_native.hip) lists the same divisions in order.
 template <typename T, bool TA, bool TB>
-int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
+int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
   // FP32 halves the matrix cores' time per k-step, so its 64x64 and 64x32
   // rings meet every second k-step (4 tiles of 64x64 per CU: 104 -> 116
   // TFLOP/s; FP64, where the deeper stage costs resident workgroups, 71 -> 66).
@@ -140,67 +142,67 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int KU32 = F64 ? 1 : 2;
   switch (cfg) {
-    case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, s);
-    case 1: return launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
-    case 2: return launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
-    case 3: return launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
-    case 4: return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, s);
-    case 5: return launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, s);
-    case 6: return launch_one<T, 128, 128, 2, 4, 1, TA, TB>(g, s);
-    case 7: return launch_one<T, 64, 64, 2, 2, 2, TA, TB>(g, s);
-    case 8: return launch_one<T, 128, 64, 4, 2, 1, TA, TB>(g, s);
-    case 9: return launch_one<T, 128, 64, 2, 2, 2, TA, TB>(g, s);
-    case 10: return launch_one<T, 256, 128, 4, 2, 1, TA, TB>(g, s);
-    case 11: return launch_one<T, 128, 256, 2, 4, 1, TA, TB>(g, s);
-    case 12: return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
-    case 13: return launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
+    case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, ks, s);
+    case 1: return launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
+    case 2: return launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
+    case 3: return launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
+    case 4: return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
+    case 5: return launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, ks, s);
+    case 6: return launch_one<T, 128, 128, 2, 4, 1, TA, TB>(g, ks, s);
+    case 7: return launch_one<T, 64, 64, 2, 2, 2, TA, TB>(g, ks, s);
+    case 8: return launch_one<T, 128, 64, 4, 2, 1, TA, TB>(g, ks, s);
+    case 9: return launch_one<T, 128, 64, 2, 2, 2, TA, TB>(g, ks, s);
+    case 10: return launch_one<T, 256, 128, 4, 2, 1, TA, TB>(g, ks, s);
+    case 11: return launch_one<T, 128, 256, 2, 4, 1, TA, TB>(g, ks, s);
+    case 12: return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
+    case 13: return launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 14:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, s)
-                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, ks, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 15:
-      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 4, TA, TB>(g, s)
-                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 4, TA, TB>(g, ks, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
     case 16:
-      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 4, TA, TB>(g, s)
-                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 4, TA, TB>(g, ks, s)
+                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 17:
-      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, s)
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s)
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 18:
-      return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, s)
-                    : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
+                    : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 19:
-      return dma_ok ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, s)
-                    : launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, ks, s)
+                    : launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
     case 20:
-      return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, s)
-                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, ks, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 21:
-      return dma_ok ? (F64 ? launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, s)
-                           : launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, s))
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
+      return dma_ok ? (F64 ? launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, ks, s)
+                           : launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, ks, s))
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 22:
-      return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, s)
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, ks, s)
+                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 23:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 1, KU32>(g, s)
-                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 1, KU32>(g, ks, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 24:
-      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, s)
-                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, ks, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
     case 25: return launch_naive<T, TA, TB>(g, s);
     case 26:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2, 2>(g, s)
-                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2, 2>(g, ks, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 27:
-      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, s)
-                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, ks, s)
+                    : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 28:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, s)
-                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, ks, s)
+                    : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 29:
-      return dma_ok ? launch_dma<T, 64, 32, 2, 1, F64 ? 2 : 3, TA, TB, 2, KU32>(g, s)
-                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, s);
+      return dma_ok ? launch_dma<T, 64, 32, 2, 1, F64 ? 2 : 3, TA, TB, 2, KU32>(g, ks, s)
+                    : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
   }
   set_error("unknown tile cfg %d", cfg);
   return MG_ERR_INVALID_ARG;
@@ -209,7 +211,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, hipStream_t s) {
 template <typename T, bool TA, bool TB>
 int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const void *A,
                  int64_t lda, const void *B, int64_t ldb, double beta, void *C, int64_t ldc,
-                 hipStream_t s) {
+                 const PartPlan &pp, hipStream_t s) {
   GemmArgs<T> g;
   g.A = static_cast<const T *>(A);
   g.B = static_cast<const T *>(B);
@@ -223,7 +225,8 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
   g.alpha = (T)alpha;
   g.beta = (T)beta;
   const bool dma_ok = ring_operands(sizeof(T) == 8 ? MG_F64 : MG_F32, A, lda, B, ldb);
-  return launch_cfg<T, TA, TB>(cfg, dma_ok, g, s);
+  const KSplit<T> ks = {static_cast<T *>(pp.planes), pp.parts, pp.kpart};
+  return launch_cfg<T, TA, TB>(cfg, dma_ok, g, ks, s);
 }
 
 }  // namespace
@@ -233,10 +236,10 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
 template <bool TA, bool TB>
 int gemm_tiles(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha, const void *A,
                int64_t lda, const void *B, int64_t ldb, double beta, void *C, int64_t ldc,
-               hipStream_t s) {
+               const PartPlan &pp, hipStream_t s) {
   if (dtype == MG_F64)
-    return gemm_tiles_t<double, TA, TB>(cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
-  return gemm_tiles_t<float, TA, TB>(cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
+    return gemm_tiles_t<double, TA, TB>(cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, pp, s);
+  return gemm_tiles_t<float, TA, TB>(cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, pp, s);
 }
 
 }  // namespace mg

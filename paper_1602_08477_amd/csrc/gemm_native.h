@@ -20,6 +20,22 @@ int pick_division(int dtype, bool ring, int64_t m, int64_t n);
 // plus a row of the tile).
 bool ring_operands(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
 
+// How a product's k range is cut over workgroups (parts == 1: not): `parts`
+// ranges of `kpart` k, partial sums in `planes` (parts x m x n elements).
+struct PartPlan {
+  void *planes = nullptr;
+  int parts = 1, kpart = 0;
+};
+
+// mg_gemm's route for operands of any kind (arguments already validated): the
+// picked division, with k cut into parts where the output has too few tiles
+// for the chip and k is long.  The partial sums' workspace comes from the
+// stream-ordered pool; under stream capture, or when the pool cannot give it,
+// the product runs uncut.
+int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double alpha,
+                     const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
+                     int64_t ldc, hipStream_t s);
+
 // Enqueues C <- alpha*A*B + beta*C with work division `cfg` (arguments
 // already validated).
 int gemm_native(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha, const void *A,
@@ -37,7 +53,7 @@ int gemm_native_op(int dtype, int cfg, bool ta, bool tb, int64_t m, int64_t n, i
 #define MG_GEMM_TILES_DECL(name)                                                               \
   int name(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha, const void *A,   \
            int64_t lda, const void *B, int64_t ldb, double beta, void *C, int64_t ldc,         \
-           hipStream_t s)
+           const PartPlan &pp, hipStream_t s)
 MG_GEMM_TILES_DECL(gemm_tiles_nn);
 MG_GEMM_TILES_DECL(gemm_tiles_tn);
 MG_GEMM_TILES_DECL(gemm_tiles_nt);

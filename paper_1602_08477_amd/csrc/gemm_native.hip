@@ -2,7 +2,10 @@
 // tiling), work division chosen per shape on the host.  This unit holds the
 // plain-layout kernels and the host side; the transposed layouts are built
 // in gemm_op_*.hip.
+#include <algorithm>
+
 #include "gemm_launch.h"
+#include "split.h"
 
 namespace mg {
 
@@ -87,13 +90,14 @@ bool ring_operands(int dtype, const void *A, int64_t lda, const void *B, int64_t
 
 namespace {
 
-// Measured rate (TFLOP/s, whole chip, k = 2048) of a work division when every
-// CU has 1, 2, 3-5 and 6 or more of its tiles to run.  A tile takes as long
+// Measured rate (TFLOP/s, whole chip, k = 2048, the launch itself taken off)
+// of a work division when every CU has 1, 2, 3-5 and 6 or more of its tiles
+// to run.  A tile takes as long
 // whether it is full or reaches past the matrix, and the CU with the most
 // tiles ends last, so a division's time is ceil(tiles / CUs) tiles at that
 // rate: 128x128 tiles are the fastest per flop, but n = 3000 gives some CUs
 // three of them and the others two (683 us by this count; 64x64 tiles: nine
-// on every CU, 520 us; measured 1092 -> 821 us).
+// on every CU, 520 us; measured 1092 -> 786 us).
 struct TileRate {
   int cfg;
   float r[4];
@@ -101,23 +105,23 @@ struct TileRate {
 constexpr TileRate kRing64[] = {{21, {70.f, 71.3f, 72.f, 73.f}},
                                 {23, {64.4f, 67.4f, 70.5f, 71.3f}},
                                 {15, {59.2f, 63.3f, 65.5f, 66.5f}},
-                                {19, {48.f, 57.f, 60.f, 62.f}}};
+                                {19, {57.f, 59.f, 61.f, 62.f}}};
 constexpr TileRate kRing32[] = {{22, {120.6f, 130.1f, 131.5f, 133.f}},
                                 {21, {126.f, 127.7f, 128.5f, 128.7f}},
                                 {23, {106.7f, 110.7f, 115.f, 119.f}},
                                 {15, {99.3f, 106.f, 107.f, 111.f}},
-                                {19, {85.8f, 98.5f, 102.5f, 109.f}}};
+                                {19, {104.f, 104.f, 105.f, 109.f}}};
 // Operands the rings cannot load: the register-staged divisions.
 constexpr TileRate kReg64[] = {{5, {61.6f, 67.9f, 67.8f, 68.f}},
                                {8, {58.f, 64.5f, 65.f, 66.f}},
                                {2, {52.5f, 62.4f, 64.5f, 66.8f}},
-                               {3, {42.9f, 49.6f, 54.f, 55.3f}},
-                               {4, {30.7f, 42.8f, 47.f, 49.f}}};
+                               {3, {46.f, 51.f, 54.f, 55.3f}},
+                               {4, {36.f, 44.f, 47.f, 49.f}}};
 constexpr TileRate kReg32[] = {{5, {116.7f, 126.9f, 128.5f, 129.f}},
                                {8, {110.7f, 117.f, 119.f, 121.f}},
                                {2, {81.f, 103.f, 117.f, 124.f}},
                                {3, {74.9f, 96.1f, 106.5f, 112.f}},
-                               {4, {56.1f, 80.2f, 91.f, 98.f}}};
+                               {4, {68.f, 84.f, 92.f, 98.f}}};
 constexpr int64_t kCus = 256;
 
 // Flops per CU of `units` workgroups of one division, over its rate.
@@ -174,8 +178,132 @@ int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k) {
 
 int gemm_tiles_nn(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha,
                   const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
-                  int64_t ldc, hipStream_t s) {
-  return gemm_tiles<false, false>(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
+                  int64_t ldc, const PartPlan &pp, hipStream_t s) {
+  return gemm_tiles<false, false>(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, pp, s);
+}
+
+namespace {
+
+// C <- alpha * (sum of the planes, in order) + beta * C: one output per lane,
+// consecutive lanes along a plane.  FP32 sums are added in FP64 and rounded
+// once.
+template <typename T>
+__global__ __launch_bounds__(256) void add_parts_kernel(const T *planes, int parts, T *C,
+                                                        int64_t ldc, int m, int n, T alpha,
+                                                        T beta) {
+  const int64_t total = (int64_t)m * n;
+  const int64_t e = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (e >= total) return;
+  double s = 0.0;
+#pragma unroll 4
+  for (int z = 0; z < parts; ++z) s += (double)planes[z * total + e];
+  T *c = C + e / n * ldc + e % n;
+  *c = beta != T(0) ? fma(alpha, (T)s, beta * *c) : alpha * (T)s;
+}
+
+// Whether and how to cut k.  A product whose tiles fill the chip badly and
+// whose k is long (384 x 384 x 8192 FP64: 144 tiles of 32x32, each a chain of
+// 512 k-steps: 69 us with 16-byte rows, 123 us without) runs `parts` times the
+// workgroups on 1/parts of the k-steps each (49 us either way); that costs
+// the partial sums' write and read and a second launch.  Both sides are
+// counted in microseconds: the division's by its rate (kOverK: the k-steps'
+// worth of time a part takes to fill and drain its ring), the planes at the
+// rate a copy reaches from the L2 and the Infinity Cache, the launch as
+// measured.  The host spends about 26 us on a cut call (the workspace and two
+// launches), so no cut call counts for less.  The cut must win by a fifth
+// (64 x 64 x 16384: 130 -> 29 us; 512 x 512 x 2048: 21 us uncut, not cut).
+struct PartChoice {
+  int cfg, parts, kpart;
+};
+
+PartChoice choose_parts(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
+  constexpr int64_t kMinK = 1024;           // shorter k: nothing to win
+  constexpr int64_t kMaxBytes = 64 << 20;   // of partial sums
+  constexpr double kOverK = 64, kLaunchUs = 5, kPlaneGBps = 3500, kHostUs = 26;
+  const int cfg = pick_division(dtype, ring, m, n);
+  PartChoice best = {cfg, 1, 0};
+  if (k < kMinK) return best;
+  const bool f64 = dtype == MG_F64;
+  const int64_t esz = f64 ? 8 : 4, bk = 128 / esz, steps = ceil_div(k, bk);
+  auto find = [&](int c) -> const TileRate * {
+    auto in = [&](const auto &tab) -> const TileRate * {
+      for (const TileRate &t : tab)
+        if (t.cfg == c) return &t;
+      return nullptr;
+    };
+    return ring ? (f64 ? in(kRing64) : in(kRing32)) : (f64 ? in(kReg64) : in(kReg32));
+  };
+  // one flop-per-CU unit of division_cost takes 2 * kCus * 1e-6 us per k
+  auto us = [&](const TileRate &t, int64_t units, double kk) {
+    return division_cost(t, units) * kk * 2.0 * kCus * 1e-6;
+  };
+  const TileRate *t1 = find(cfg);
+  if (t1 == nullptr) return best;  // a two-k-group division: the chip is full
+  const double uncut = us(*t1, tiles_of(cfg, m, n), (double)k + kOverK);
+  double least = 0.8 * uncut;
+  if (least <= kHostUs) return best;
+  const int candidates[2] = {ring ? 23 : 2, ring ? 19 : 4};
+  for (int c : candidates) {
+    const TileRate *t = find(c);
+    const int64_t tiles = tiles_of(c, m, n);
+    for (int64_t parts = 2; parts <= 64 && parts <= steps / 4; ++parts) {
+      const int64_t kpart = ceil_div(steps, parts) * bk;
+      if (ceil_div(k, kpart) != parts) continue;
+      const double bytes = (double)parts * m * n * esz;
+      if (bytes > (double)kMaxBytes) break;
+      const double cost = std::max(kHostUs, us(*t, tiles * parts, (double)kpart + kOverK) +
+                                                kLaunchUs + 2.0 * bytes / (kPlaneGBps * 1e3));
+      if (cost < least) {
+        least = cost;
+        best = {c, (int)parts, (int)kpart};
+      }
+    }
+  }
+  return best;
+}
+
+template <typename T>
+int add_parts(const PartPlan &pp, int64_t m, int64_t n, double alpha, double beta, void *C,
+              int64_t ldc, hipStream_t s) {
+  const int64_t blocks = ceil_div(m * n, 256);
+  hipLaunchKernelGGL(add_parts_kernel<T>, dim3((unsigned)blocks), dim3(256), 0, s,
+                     static_cast<const T *>(pp.planes), pp.parts, static_cast<T *>(C), ldc, (int)m,
+                     (int)n, (T)alpha, (T)beta);
+  MG_HIP_TRY(hipGetLastError());
+  return MG_OK;
+}
+
+}  // namespace
+
+int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double alpha,
+                     const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
+                     int64_t ldc, hipStream_t s) {
+  const bool ring = ring_operands(dtype, A, lda, B, ldb);
+  PartChoice pc = {pick_division(dtype, ring, m, n), 1, 0};
+  if (m > 0 && n > 0 && alpha != 0.0) pc = choose_parts(dtype, ring, m, n, k);
+  if (pc.parts > 1) {
+    PartPlan pp;
+    const int64_t bytes = (int64_t)pc.parts * m * n * (dtype == MG_F64 ? 8 : 4);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        pool_alloc(&pp.planes, bytes, s) == MG_OK) {
+      pp.parts = pc.parts;
+      pp.kpart = pc.kpart;
+      auto run = ta ? (tb ? gemm_tiles_tt : gemm_tiles_tn) : (tb ? gemm_tiles_nt : gemm_tiles_nn);
+      int rc = run(dtype, pc.cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, pp, s);
+      if (rc == MG_OK)
+        rc = dtype == MG_F64 ? add_parts<double>(pp, m, n, alpha, beta, C, ldc, s)
+                             : add_parts<float>(pp, m, n, alpha, beta, C, ldc, s);
+      const hipError_t e = hipFreeAsync(pp.planes, s);
+      if (rc != MG_OK) return rc;
+      MG_HIP_TRY(e);
+      return MG_OK;
+    }
+    (void)hipGetLastError();
+    clear_error();
+    pc.cfg = pick_division(dtype, ring, m, n);
+  }
+  return gemm_native_op(dtype, pc.cfg, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
 }
 
 int gemm_native_op(int dtype, int cfg, bool ta, bool tb, int64_t m, int64_t n, int64_t k,
@@ -190,7 +318,7 @@ int gemm_native_op(int dtype, int cfg, bool ta, bool tb, int64_t m, int64_t n, i
     return dtype == MG_F64 ? scale_c<double>(m, n, beta, C, ldc, s)
                            : scale_c<float>(m, n, beta, C, ldc, s);
   auto run = ta ? (tb ? gemm_tiles_tt : gemm_tiles_tn) : (tb ? gemm_tiles_nt : gemm_tiles_nn);
-  return run(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
+  return run(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, PartPlan{}, s);
 }
 
 int gemm_native(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha, const void *A,

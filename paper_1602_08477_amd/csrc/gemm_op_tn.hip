@@ -6,8 +6,8 @@ namespace mg {
 
 int gemm_tiles_tn(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha,
                   const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
-                  int64_t ldc, hipStream_t s) {
-  return gemm_tiles<true, false>(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
+                  int64_t ldc, const PartPlan &pp, hipStream_t s) {
+  return gemm_tiles<true, false>(dtype, cfg, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, pp, s);
 }
 
 }  // namespace mg

@@ -82,6 +82,32 @@ struct GemmArgs {
   T alpha, beta;
 };
 
+// Split of a product's k range over workgroups: part z sums k in [z*kpart,
+// (z+1)*kpart) into its own m x n plane of `planes` (pitch n), and a second
+// kernel adds the planes in order.  parts == 1: no split.
+template <typename T>
+struct KSplit {
+  T *planes;
+  int parts, kpart;
+};
+
+// The part of workgroup t of tiles * parts (tile t % tiles of part t / tiles):
+// `g` becomes that part's product, C <- A B into its plane.
+template <typename T, bool TA, bool TB>
+__device__ __forceinline__ int take_part(GemmArgs<T> &g, const KSplit<T> &ks, int t, int tiles) {
+  if (ks.parts == 1) return t;
+  const int z = t / tiles;
+  const int64_t k0 = (int64_t)z * ks.kpart;
+  g.A += TA ? k0 * g.lda : k0;
+  g.B += TB ? k0 : k0 * g.ldb;
+  g.C = ks.planes + (int64_t)z * g.m * g.n;
+  g.ldc = g.n;
+  g.k = min(ks.kpart, g.k - (int)k0);
+  g.alpha = T(1);
+  g.beta = T(0);
+  return t - z * tiles;
+}
+
 constexpr int kTileThreads = 256;
 
 // Macro-tile BM x BN computed by WGM x WGN wavefronts (each a WM x WN wave

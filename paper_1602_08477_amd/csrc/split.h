@@ -64,6 +64,8 @@ int gemm_split_pooled(int algo, int slices, int64_t m, int64_t n, int64_t k, dou
 // The library's stream-ordered pool for split workspaces on the current
 // device (freed blocks are kept for reuse), and a trim of every such pool.
 int workspace_pool(hipMemPool_t *out);
+// Stream-ordered workspace from that pool (released with hipFreeAsync).
+int pool_alloc(void **p, int64_t bytes, hipStream_t s);
 int release_workspace_pools();
 
 // Device workspace and pinned host staging that a caller who runs batches one

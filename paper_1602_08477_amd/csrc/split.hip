@@ -1771,9 +1771,6 @@ int release_workspace_pools() {
   return MG_OK;
 }
 
-namespace {
-
-// Stream-ordered workspace from the library's pool.
 int pool_alloc(void **p, int64_t bytes, hipStream_t s) {
   hipMemPool_t pool = nullptr;
   int rc = workspace_pool(&pool);
@@ -1786,8 +1783,6 @@ int pool_alloc(void **p, int64_t bytes, hipStream_t s) {
   }
   return MG_OK;
 }
-
-}  // namespace
 
 int gemm_split_pooled(int algo, int slices, int64_t m, int64_t n, int64_t k, double alpha,
                       const double *A, int64_t lda, const double *B, int64_t ldb, double beta,

@@ -130,7 +130,7 @@ mg::GemmArgs<double> args(const Mats &m) {
 template <typename K>
 void direct(K kern, dim3 grid, int threads, size_t lds, const mg::GemmArgs<double> &g, int tm,
             int tn, hipStream_t s) {
-  hipLaunchKernelGGL(kern, grid, dim3(threads), lds, s, g, tm, tn);
+  hipLaunchKernelGGL(kern, grid, dim3(threads), lds, s, g, tm, tn, mg::KSplit<double>{nullptr, 1, 0});
 }
 
 void one_shape(int n, int reps, hipStream_t s, bool first) {
