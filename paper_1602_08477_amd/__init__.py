@@ -101,39 +101,65 @@ def check(rc: int) -> int:
 
 
 # ------------------------------------------------------------------ helpers
-def _stream_handle(stream):
+# A small product's kernel is shorter than its call (64 x 64 x 64 FP64: about
+# 2 us against 9.4 us of host time per call, of which torch.cuda.current_stream()
+# took 2.6 and the three operands' descriptors 4), so these helpers build
+# nothing but plain integers: 9.4 -> 5.3 us.
+def _current_stream() -> int:
+    """Handle of torch's current stream on the current device."""
+    global _current_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    try:
+        device, raw = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+        def current() -> int:
+            return raw(device())
+    except AttributeError:  # a torch without the raw accessors
+        def current() -> int:
+            return torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()  # initialises torch's CUDA state, once
+    _current_stream = current  # later calls skip the import and the look-up
+    return current()
+
+
+def _stream_handle(stream) -> int:
+    return _current_stream() if stream is None else stream.cuda_stream
+
+
+_dtype_codes = {}
 
 
 def _dtype_code(t) -> int:
-    import torch
-    if t.dtype == torch.float64:
-        return F64
-    if t.dtype == torch.float32:
-        return F32
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
+        import torch
+        _dtype_codes.update({torch.float64: F64, torch.float32: F32})
+        code = _dtype_codes.get(t.dtype)
+        if code is None:
+            raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _mat(t, name):
     """(pointer, rows, cols, ld) of a row-major 2-D tensor with unit column stride."""
     if t is None:
         return None, 0, 0, 1
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError(f"{name} must be 2-D")
-    if t.shape[1] > 1 and t.stride(1) != 1:
+    rows, cols = shape
+    s0, s1 = t.stride()
+    if s1 != 1 and cols > 1:
         raise ValueError(f"{name} must have unit column stride (row-major)")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.shape[1], 1)
-    return ctypes.c_void_p(t.data_ptr()), t.shape[0], t.shape[1], max(ld, t.shape[1], 1)
+    if rows <= 1 or s0 < cols:
+        s0 = cols
+    return t.data_ptr(), rows, cols, s0 or 1
 
 
 def _mnk(A, B, C, k):
     pa, am, ak, lda = _mat(A, "A")
     pb, bk, bn, ldb = _mat(B, "B")
-    pc, cm, cn, ldc = _mat(C, "C")
-    m, n = cm, cn
+    pc, m, n, ldc = _mat(C, "C")
     if A is not None:
         k = ak
         if am != m:
@@ -151,11 +177,14 @@ def gemm(A, B, C, alpha: float = 1.0, beta: float = 0.0, algo: int = NATIVE,
     A may be None only with k == 0.  Returns C."""
     (pa, lda), (pb, ldb), (pc, ldc), m, n, kk = _mnk(A, B, C, k)
     dt = _dtype_code(C)
-    s = _stream_handle(stream)
+    s = _current_stream() if stream is None else stream.cuda_stream
+    L = _lib or lib()
     if cfg is None:
-        check(lib().mg_gemm(dt, algo, m, n, kk, alpha, pa, lda, pb, ldb, beta, pc, ldc, s))
+        rc = L.mg_gemm(dt, algo, m, n, kk, alpha, pa, lda, pb, ldb, beta, pc, ldc, s)
     else:
-        check(lib().mg_gemm_cfg(dt, cfg, m, n, kk, alpha, pa, lda, pb, ldb, beta, pc, ldc, s))
+        rc = L.mg_gemm_cfg(dt, cfg, m, n, kk, alpha, pa, lda, pb, ldb, beta, pc, ldc, s)
+    if rc < 0:
+        check(rc)
     return C
 
 
@@ -181,16 +210,17 @@ def daxpy(alpha: float, x, y, stream=None):
     """y <- alpha*x + y in place (mg_daxpy).  x and y are 1-D float64 CUDA
     tensors of equal length; their strides (>= 1) are the increments.
     Returns y."""
-    for t, name in ((x, "x"), (y, "y")):
-        if t.dim() != 1:
-            raise ValueError(f"{name} must be 1-D")
-    if x.shape[0] != y.shape[0]:
-        raise ValueError("x and y lengths differ")
+    if x.dim() != 1:
+        raise ValueError("x must be 1-D")
+    if y.dim() != 1:
+        raise ValueError("y must be 1-D")
     n = y.shape[0]
+    if x.shape[0] != n:
+        raise ValueError("x and y lengths differ")
     incx = x.stride(0) if n > 1 else 1
     incy = y.stride(0) if n > 1 else 1
-    check(lib().mg_daxpy(n, alpha, ctypes.c_void_p(x.data_ptr()), incx,
-                         ctypes.c_void_p(y.data_ptr()), incy, _stream_handle(stream)))
+    check(lib().mg_daxpy(n, alpha, x.data_ptr(), incx, y.data_ptr(), incy,
+                         _stream_handle(stream)))
     return y
 
 
@@ -232,7 +262,7 @@ def split_prepare(algo: int, slices: int, A, B, workspace, stream=None):
     if kb != k:
         raise ValueError("inner dimensions differ")
     check(lib().mg_split_prepare(algo, slices, m, n, k, pa, lda, pb, ldb,
-                                 ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                 workspace.data_ptr(), workspace.numel(),
                                  _stream_handle(stream)))
     return workspace
 
@@ -261,7 +291,7 @@ def gemm_split(A, B, C, alpha: float = 1.0, beta: float = 0.0, algo: int = SPLIT
     if workspace is None:
         workspace = split_workspace(algo, slices, m, n, k, device=C.device)
     check(lib().mg_gemm_split_cfg(algo, slices, cfg, m, n, k, alpha, pa, lda, pb, ldb, beta, pc,
-                                  ldc, ctypes.c_void_p(workspace.data_ptr()), workspace.numel(),
+                                  ldc, workspace.data_ptr(), workspace.numel(),
                                   _stream_handle(stream)))
     return C
 
