@@ -238,14 +238,14 @@ int mg_release_cached_memory(void);
 
 /* ------------------------------------------------------- batched GEMM --
  * Many independent problems C_i <- alpha_i A_i B_i + beta_i C_i (each the
- * Section 4.2 operation) in ONE persistent launch.  A plan validates the
+ * Section 4.2 operation) in ONE launch.  A plan validates the
  * problems, picks a tile class per problem (from a tuning table or a
  * heuristic), builds a device work list of macro-tiles sorted longest first
  * (each record carries its problem's arguments), and on first launch
- * captures the persistent kernel in a HIP graph that later launches replay.
- * The grid is (CUs x occupancy) workgroups G; the list is dealt in rounds
- * of G tiles whose direction alternates (workgroup b takes tile b of round
- * 0, G-1-b of round 1, ...).  Blocks are independent and never synchronise
+ * captures the launch in a HIP graph that later launches replay.
+ * The launch runs one workgroup per tile in list order; within each round of
+ * (CUs x occupancy) workgroups, the ones resident at once, an XCD takes a
+ * contiguous run of tiles.  Blocks are independent and never synchronise
  * (Section 3.2), and every tile sums its k-steps in the order of the
  * single-problem kernels with one k group of wavefronts, so a problem's
  * result is the same whatever else is in the batch, and bit for bit equal to
@@ -283,7 +283,8 @@ typedef struct mg_tune_table {
 } mg_tune_table;
 
 typedef struct mg_plan_stats {
-  int64_t problems, tiles, workgroups, occupancy;
+  int64_t problems, tiles;
+  int64_t workgroups, occupancy; /* resident at once; per CU                  */
   int64_t tiles_per_class[MG_NUM_GROUPED_CLASSES];
   int64_t scale_tiles; /* tiles of problems with alpha == 0 or k == 0        */
   double flops;        /* sum of 2mnk                                        */
@@ -297,11 +298,13 @@ typedef struct mg_plan mg_plan;
 int mg_grouped_class_info(int cls, int *bm, int *bn);
 /* Index of (m, n, k) in mg_tune_table.cls. */
 int mg_tune_bucket(int64_t m, int64_t n, int64_t k);
-/* Heuristic table (largest tile wasting at most a quarter of its area). */
+/* Heuristic table: the class with the least modelled time at each bucket's
+ * representative shape (without a table, plans apply the same model to each
+ * problem's own extents). */
 int mg_tune_default(int dtype, mg_tune_table *out);
 /* Autotuner: for every bucket, times each tile class on a batch of problems
  * of the bucket's representative shape, as many (48 to 4096) as it takes for
- * the largest class to give every workgroup slot of the persistent kernel
+ * the largest class to give every workgroup slot of the batched kernel
  * four tiles, so that classes compete on throughput in a full batch (reps
  * launches on `stream`, HIP events), and records the fastest.  Allocates and
  * frees its own scratch operands (about 0.4 GB for FP64); blocks until done.
@@ -370,7 +373,7 @@ int mg_gemm_batched_cache_stats(int64_t *hits, int64_t *misses);
  * process ends; about 87 000 FP64 tiles) instead of library-allocated memory:
  * the call makes no hipMalloc/hipFree and creates no event.  It copies the
  * work list from host memory into that array on `stream` and launches the
- * persistent kernel behind it.  Every call on a GPU shares that GPU's
+ * batched kernel behind it.  Every call on a GPU shares that GPU's
  * array: calls on one stream are ordered, but calls that overlap on one GPU
  * (other streams, other threads, before an earlier launch has finished on
  * another stream) race on it.  MG_ERR_INVALID_ARG (nothing enqueued) for a
@@ -384,7 +387,7 @@ int mg_gemm_batched_noalloc(int dtype, int64_t count, const mg_problem *probs, v
  * but-unfinished requests stay within `max_slots` and their bytes (A + B + C,
  * plus the split workspace for split requests) within `hbm_budget_bytes`, and
  * launches everything admitted so far as one batch on the next free stream
- * (one persistent grouped launch for the native requests, one batched split
+ * (one grouped launch for the native requests, one batched split
  * launch set per split algorithm, as in mg_gemm_batched; each stream keeps
  * its own grow-only device workspace and pinned staging buffer for these,
  * so a batch allocates only when it needs more than any batch before it on

@@ -398,7 +398,7 @@ def autotune(dtype: int = F64, reps: int = 3, stream=None, cache: str | None = N
 
 
 class Plan:
-    """A batch of problems prepared for one persistent (graph-replayed) launch."""
+    """A batch of problems prepared for one (graph-replayed) launch."""
 
     def __init__(self, dtype, probs, table: TuneTable | None = None, keep=None):
         arr, n = _problems(probs)

@@ -225,7 +225,7 @@ extern "C" {
 
 const char *mg_last_error(void) { return g_err; }
 
-int mg_version(void) { return 10100; }
+int mg_version(void) { return 10200; }
 
 int mg_build_flags(void) {
 #ifdef MG_LDS_POISON
@@ -486,7 +486,7 @@ int mg_tune_default(int dtype, mg_tune_table *out) {
     for (int bn = 0; bn < kTuneEdges; ++bn)
       for (int bk = 0; bk < kTuneEdges; ++bk)
         out->cls[(bm * kTuneEdges + bn) * kTuneEdges + bk] =
-            heuristic_class(tune_bucket_rep(bm), tune_bucket_rep(bn));
+            heuristic_class(dtype, tune_bucket_rep(bm), tune_bucket_rep(bn), tune_bucket_rep(bk));
   return MG_OK;
 }
 

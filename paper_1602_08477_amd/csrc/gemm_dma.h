@@ -521,10 +521,10 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs<T> &g, int m0, int 
   if constexpr (PAIR)
     store_paired_f64<S::FM, S::FN, S::FM, S::FN, PAIRA>(g, acc, m0 + wm0, n0 + wn0, lane);
   else if constexpr (ESZ == 8)
-    Epilogue<T, true>::template store<S::FM, S::FN, S::FM, S::FN, PAIRA>(g, acc, m0 + wm0,
+    Epilogue<T>::template store<S::FM, S::FN, S::FM, S::FN, PAIRA>(g, acc, m0 + wm0,
                                                                     n0 + wn0, lane);
   else
-    Epilogue<T, true>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
+    Epilogue<T>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
 }
 
 }  // namespace mg

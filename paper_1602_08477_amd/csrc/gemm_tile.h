@@ -5,7 +5,7 @@
 // threads stage tiles of A and B in shared memory (LDS), every thread
 // accumulates a set of elements, and the block then moves on to the next
 // A/B tiles along k.  Mapped to CDNA4:
-//   grid    -> one dispatch (or a persistent loop over tiles)
+//   grid    -> one dispatch
 //   block   -> workgroup of 256 lanes = 4 wavefronts in a 2 x 2 arrangement
 //   thread  -> lane; its registers hold (BM/32)*(BN/32) MFMA accumulators
 //   element -> 16x16 MFMA fragments (4 values per lane) and 16-byte loads
@@ -218,73 +218,80 @@ __device__ __forceinline__ int f64_out_row(int row0, int i, int gq, int r) {
 
 // C tile epilogue for a wave's FM x FN grid of 16x16 blocks whose top-left
 // output is (row0, col0): out = alpha*acc + beta*C (C unread when beta == 0).
-// In block (i, j), lane l holds column l%16 of rows row_of(l/16, r).  One
-// block row i at a time, all its C loads are issued before its first store,
-// so they are in flight together instead of each waiting behind the previous
-// store (and the extra registers stay at one block row's worth).
-// FP64: neighbouring lanes (same rows, columns c and c+1) swap one value each
-// so that each lane owns a 16-byte pair of adjacent columns of one row.
-// VEC: C moves in those pairs, at any 8-byte address (FP64).
-template <typename T, bool VEC>
+// In block (i, j), lane l holds column l%16 of rows row_of(l/16, r).  The C
+// loads of a few block rows are all issued before the first store, so they
+// are in flight together instead of each waiting behind the previous store.
+// FP32 loads come from addresses clamped into the matrix, without lane
+// branches (2000 problems in one launch: 265 -> 240 us); FP64 pairs are masked
+// (clamped ones, read twice at the edges: 414 -> 443 us).
+
+// Block rows whose C is in flight at once: all of a small wave tile's (the
+// registers of its k loop are free by now), one of a large one's.
+template <int FM, int FN>
+constexpr int kEpilogueRows = FM * FN <= 4 ? FM : 1;
+
+// Columns col, col+1 of row `row`; zeros past the matrix.
+__device__ __forceinline__ d2v load_c_pair(const GemmArgs<double> &g, int row, int col) {
+  d2v x = {0.0, 0.0};
+  if (row >= g.m) return x;
+  const double *p = g.C + (int64_t)row * g.ldc + col;
+  if (col + 1 < g.n) x = Chunk<double>::load(p);
+  else if (col < g.n) x[0] = p[0];
+  return x;
+}
+
+__device__ __forceinline__ void store_c_pair(const GemmArgs<double> &g, int row, int col, d2v v,
+                                             d2v c, bool use_c) {
+  if (row >= g.m) return;
+  d2v o;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) o[e] = use_c ? fma(g.alpha, v[e], g.beta * c[e]) : g.alpha * v[e];
+  double *p = g.C + (int64_t)row * g.ldc + col;
+  if (col + 1 < g.n) Chunk<double>::store(p, o);
+  else if (col < g.n) p[0] = o[0];
+}
+
+template <typename T>
 struct Epilogue;
 
-template <bool VEC>
-struct Epilogue<double, VEC> {
+// FP64: neighbouring lanes (same rows, columns c and c+1) swap one value each
+// so that each lane owns a 16-byte pair of adjacent columns of one row.
+template <>
+struct Epilogue<double> {
   template <int FM, int FN, int AM, int AN, bool PA = false>
   __device__ static __forceinline__ void store(const GemmArgs<double> &g,
                                                const d4v (&acc)[AM][AN], int row0, int col0,
                                                int lane) {
+    constexpr int R = kEpilogueRows<FM, FN>;
     const int gq = lane >> 4, j = lane & 15;
     const bool odd = j & 1;
     const bool use_c = g.beta != 0.0;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      d2v v[FN][2], c[FN][2];
+    for (int i0 = 0; i0 < FM; i0 += R) {
+      d2v c[R][FN][2] = {};
+      if (use_c) {
 #pragma unroll
-      for (int jb = 0; jb < FN; ++jb)
+        for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int r = 2 * h;
-          const double send = odd ? acc[i][jb][r] : acc[i][jb][r + 1];
-          const double got = dpp_swap1(send);
-          v[jb][h][0] = odd ? got : acc[i][jb][r];
-          v[jb][h][1] = odd ? acc[i][jb][r + 1] : got;
-        }
+          for (int jb = 0; jb < FN; ++jb)
 #pragma unroll
-      for (int jb = 0; jb < FN; ++jb)
+            for (int h = 0; h < 2; ++h)
+              c[i][jb][h] = load_c_pair(g, f64_out_row<PA>(row0, i0 + i, gq, 2 * h + (odd ? 1 : 0)),
+                                        col0 + 16 * jb + (j & ~1));
+      }
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = f64_out_row<PA>(row0, i, gq, 2 * h + (odd ? 1 : 0));
-          const int col = col0 + 16 * jb + (j & ~1);
-          c[jb][h] = d2v{0.0, 0.0};
-          if (!use_c || row >= g.m) continue;
-          const double *p = g.C + (int64_t)row * g.ldc + col;
-          if (VEC && col + 1 < g.n) {
-            c[jb][h] = Chunk<double>::load(p);
-          } else {
-            if (col < g.n) c[jb][h][0] = p[0];
-            if (col + 1 < g.n) c[jb][h][1] = p[1];
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int jb = 0; jb < FN; ++jb)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const d4v &s = acc[i0 + i][jb];
+            const int r = 2 * h;
+            const double got = dpp_swap1(odd ? s[r] : s[r + 1]);
+            const d2v v = {odd ? got : s[r], odd ? s[r + 1] : got};
+            store_c_pair(g, f64_out_row<PA>(row0, i0 + i, gq, r + (odd ? 1 : 0)),
+                         col0 + 16 * jb + (j & ~1), v, c[i][jb][h], use_c);
           }
-        }
-#pragma unroll
-      for (int jb = 0; jb < FN; ++jb)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int row = f64_out_row<PA>(row0, i, gq, 2 * h + (odd ? 1 : 0));
-          const int col = col0 + 16 * jb + (j & ~1);
-          if (row >= g.m) continue;
-          d2v o;
-#pragma unroll
-          for (int e = 0; e < 2; ++e)
-            o[e] = use_c ? fma(g.alpha, v[jb][h][e], g.beta * c[jb][h][e]) : g.alpha * v[jb][h][e];
-          double *p = g.C + (int64_t)row * g.ldc + col;
-          if (VEC && col + 1 < g.n) {
-            Chunk<double>::store(p, o);
-          } else {
-            if (col < g.n) p[0] = o[0];
-            if (col + 1 < g.n) p[1] = o[1];
-          }
-        }
     }
   }
 };
@@ -299,71 +306,68 @@ __device__ __forceinline__ void store_paired_f64(const GemmArgs<double> &g,
                                                  const d4v (&acc)[AM][AN], int row0, int col0,
                                                  int lane) {
   static_assert(FN % 2 == 0, "pairs of block columns");
+  constexpr int R = kEpilogueRows<FM, FN>;
   const int gq = lane >> 4, l16 = lane & 15;
   const bool use_c = g.beta != 0.0;
 #pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    d2v c[FN / 2][4];
+  for (int i0 = 0; i0 < FM; i0 += R) {
+    d2v c[R][FN / 2][4] = {};
+    if (use_c) {
 #pragma unroll
-    for (int p = 0; p < FN / 2; ++p)
+      for (int i = 0; i < R; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = f64_out_row<PA>(row0, i, gq, r);
-        const int col = col0 + 32 * p + 2 * l16;
-        c[p][r] = d2v{0.0, 0.0};
-        if (!use_c || row >= g.m) continue;
-        const double *q = g.C + (int64_t)row * g.ldc + col;
-        if (col + 1 < g.n) c[p][r] = Chunk<double>::load(q);
-        else if (col < g.n) c[p][r][0] = q[0];
-      }
+        for (int p = 0; p < FN / 2; ++p)
 #pragma unroll
-    for (int p = 0; p < FN / 2; ++p)
+          for (int r = 0; r < 4; ++r)
+            c[i][p][r] = load_c_pair(g, f64_out_row<PA>(row0, i0 + i, gq, r),
+                                     col0 + 32 * p + 2 * l16);
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = f64_out_row<PA>(row0, i, gq, r);
-        const int col = col0 + 32 * p + 2 * l16;
-        if (row >= g.m) continue;
-        d2v o;
+    for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const double v = acc[i][2 * p + e][r];
-          o[e] = use_c ? fma(g.alpha, v, g.beta * c[p][r][e]) : g.alpha * v;
-        }
-        double *q = g.C + (int64_t)row * g.ldc + col;
-        if (col + 1 < g.n) Chunk<double>::store(q, o);
-        else if (col < g.n) q[0] = o[0];
-      }
+      for (int p = 0; p < FN / 2; ++p)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          store_c_pair(g, f64_out_row<PA>(row0, i0 + i, gq, r), col0 + 32 * p + 2 * l16,
+                       d2v{acc[i0 + i][2 * p][r], acc[i0 + i][2 * p + 1][r]}, c[i][p][r], use_c);
   }
 }
 
-template <bool VEC>
-struct Epilogue<float, VEC> {
+template <>
+struct Epilogue<float> {
   template <int FM, int FN, int AM, int AN>
   __device__ static __forceinline__ void store(const GemmArgs<float> &g,
                                                const f4v (&acc)[AM][AN], int row0, int col0,
                                                int lane) {
+    constexpr int R = kEpilogueRows<FM, FN>;
     const int gq = lane >> 4, j = lane & 15;
     const bool use_c = g.beta != 0.0f;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      float c[FN][4];
+    for (int i0 = 0; i0 < FM; i0 += R) {
+      float c[R][FN][4] = {};
+      if (use_c) {
 #pragma unroll
-      for (int jb = 0; jb < FN; ++jb)
+        for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = row0 + 16 * i + Mfma<float>::row_of(gq, r), col = col0 + 16 * jb + j;
-          c[jb][r] = 0.0f;
-          if (use_c && row < g.m && col < g.n) c[jb][r] = g.C[(int64_t)row * g.ldc + col];
-        }
+          for (int jb = 0; jb < FN; ++jb)
 #pragma unroll
-      for (int jb = 0; jb < FN; ++jb)
+            for (int r = 0; r < 4; ++r) {
+              const int row = row0 + 16 * (i0 + i) + Mfma<float>::row_of(gq, r);
+              c[i][jb][r] = g.C[(int64_t)min(row, g.m - 1) * g.ldc + min(col0 + 16 * jb + j, g.n - 1)];
+            }
+      }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int row = row0 + 16 * i + Mfma<float>::row_of(gq, r), col = col0 + 16 * jb + j;
-          if (row < g.m && col < g.n)
-            g.C[(int64_t)row * g.ldc + col] =
-                use_c ? fmaf(g.alpha, acc[i][jb][r], g.beta * c[jb][r]) : g.alpha * acc[i][jb][r];
-        }
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int jb = 0; jb < FN; ++jb)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int row = row0 + 16 * (i0 + i) + Mfma<float>::row_of(gq, r), col = col0 + 16 * jb + j;
+            const float a = acc[i0 + i][jb][r];
+            if (row < g.m && col < g.n)
+              g.C[(int64_t)row * g.ldc + col] =
+                  use_c ? fmaf(g.alpha, a, g.beta * c[i][jb][r]) : g.alpha * a;
+          }
     }
   }
 };
@@ -468,23 +472,27 @@ struct Panel {
 // Computes the BM x BN tile of C whose top-left output is (m0, n0) of
 // C <- alpha*op(A)*op(B) + beta*C (op = transpose when TA / TB is set).
 // `smem` holds 2 stages of TileShape::STAGE elements.  All THREADS lanes of
-// the workgroup must call this together (it contains barriers).
+// the workgroup must call this together (it contains barriers).  `turn` (below
+// WGM * WGN, the same for all lanes) permutes which wavefront computes which
+// part of the tile.
 template <typename T, int BM, int BN, int WGM = 2, int WGN = 2, int BKM = 1, bool TA = false,
           bool TB = false>
-__device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, T *smem) {
+__device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, T *smem,
+                                          int turn = 0) {
   typedef TileShape<T, BM, BN, WGM, WGN, BKM, TA, TB> S;
   typedef Mfma<T> M;
   typedef typename M::vec_t V;
   typedef typename M::acc_t Acc;
   constexpr int VEC = S::VEC, BK = S::BK;
   constexpr int ACH = S::ACH;  // k chunks per tile row of A (and of stored B^T)
+  constexpr int PD = S::PD;
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) ^ turn;
   const int wm0 = (wave / WGN) * S::WM, wn0 = (wave % WGN) * S::WN;
   const int gq = lane >> 4, l16 = lane & 15;
 
-  constexpr int PD = S::PD;
   Panel<T, BM, BK, S::THREADS, !TA, PD> pa;
   Panel<T, BN, BK, S::THREADS, TB, PD> pb;
   pa.init(g.A, g.lda, m0, g.m, tid);
@@ -571,6 +579,24 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
   __syncthreads();
   int kt = 0;
   if constexpr (S::AHEAD) {
+    // A 32x32 wavefront whose outputs all lie past the matrix only stages
+    // (16x16 ones cost more in the check than they save: 528 -> 567 us for
+    // 2000 problems in 32x32 tiles).
+    if (S::WM * S::WN >= 1024 && (m0 + wm0 >= g.m || n0 + wn0 >= g.n)) {
+      for (; kt < KT; kt += PD) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j) {
+          if (kt + j >= KT) break;
+          const int buf = (kt + j + 1) & 1;
+          MG_LDS_POISON_STAGE(smem + buf * S::STAGE, S::STAGE * (int)sizeof(T));
+          if (kt + j + 1 < KT)
+            store_tiles(kt + j + 1, buf, (j + 1) % PD, kt + j + 1 < KW);
+          load_any(kt + j + 1 + PD, (j + 1) % PD);
+          lds_barrier();
+        }
+      }
+      return;
+    }
     // Small wave tiles: a round's fragments are read from LDS while the
     // matrix cores work on the previous round's.  In step kt, k-tile kt+1 goes
     // to the other buffer (its last readers are behind the barrier) and the
@@ -673,7 +699,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs<T> &g, int m0, int n0, 
     }
   }
 
-  Epilogue<T, true>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
+  Epilogue<T>::template store<S::FM, S::FN>(g, acc, m0 + wm0, n0 + wn0, lane);
 }
 
 }  // namespace mg

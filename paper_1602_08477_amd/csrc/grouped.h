@@ -1,4 +1,4 @@
-// Batched (grouped) GEMM: plans, persistent kernel, graph replay, tuning.
+// Batched (grouped) GEMM: plans, the kernel over a work list, graph replay, tuning.
 #pragma once
 
 #include <vector>
@@ -18,7 +18,7 @@ struct Plan;
 int tune_bucket(int64_t m, int64_t n, int64_t k);
 int64_t tune_bucket_rep(int b);
 int grouped_class_tile(int cls, int *bm, int *bn);
-int heuristic_class(int64_t m, int64_t n);
+int heuristic_class(int dtype, int64_t m, int64_t n, int64_t k);
 
 // Host work list of a batch: tile records (device layout, problem arguments
 // inline) sorted longest first, ready to be copied to the device as bytes.
@@ -31,9 +31,11 @@ struct WorkList {
 
 int build_worklist(int dtype, int64_t count, const mg_problem *probs, const mg_tune_table *table,
                    WorkList *out);
-// Persistent grid (CUs x occupancy, at most ntiles) for the grouped kernel.
+// Workgroups of the grouped kernel resident at once (CUs x occupancy, at most
+// ntiles): the rounds its tiles are dealt to the XCDs in.
 int grouped_grid(int dtype, int ntiles, int *grid, int *occupancy);
-// Enqueues the persistent kernel over a device copy of a work list.
+// Enqueues the grouped kernel over a device copy of a work list (`grid`: from
+// grouped_grid).
 int launch_worklist(int dtype, const void *d_tiles, int ntiles, int grid, hipStream_t s);
 
 int plan_create(int dtype, int64_t count, const mg_problem *probs, const mg_tune_table *table,

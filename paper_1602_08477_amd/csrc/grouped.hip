@@ -1,17 +1,20 @@
-// Batched uneven GEMMs in one persistent launch.
+// Batched uneven GEMMs in one launch.
 //
 // A plan turns a list of independent problems C_i <- alpha_i A_i B_i +
 // beta_i C_i into a device work list of macro-tiles (each record carries its
 // problem's arguments, tile coordinates and a tile class from the tuning
-// table), sorted longest first.  One persistent kernel of (CUs x occupancy)
-// workgroups deals the list out in rounds of G tiles, alternating direction
-// (workgroup b takes tile b of round 0, G-1-b of round 1, ...: with the list
-// in decreasing cost every workgroup ends up with about the same work) and
-// runs the same per-tile arithmetic as the single-problem kernel,
-// so a problem's result does not depend on what else is in the batch.  Each
-// workgroup streams its tiles' k-steps through an LDS ring that is filled two
-// steps ahead, across tile boundaries.  The launch is captured once in a HIP
-// graph and replayed.
+// table), sorted longest first.  One launch runs a workgroup per tile in list
+// order with the single-problem kernels' register-staged tiles, so a problem's
+// result does not depend on what else is in the batch.  The launch is captured
+// once in a HIP graph and replayed.
+//
+// What bounds it: memory, for a batch of small problems.  2000 problems of
+// extents 16-512 (1.32 GB, 11.1 GFLOP, 17.9 on 64x64 tiles): 411 us in FP64 =
+// 3.2 TB/s (on 64x64 tiles alone 419 when measured: 345 without the products,
+// 325 without the C traffic, 210 with neither); FP32 241 us.  A persistent
+// kernel that streamed a workgroup's tiles through one LDS ring of 4-byte
+// loads (any alignment) took 650 and 401 us: four times the load instructions,
+// one register allocation for every path, and a static deal of the tiles.
 //
 // In the paper's terms (Section 3.2): blocks are independent and are never
 // synchronised with each other; they share nothing but the read-only list.
@@ -31,7 +34,7 @@ namespace mg {
 
 namespace {
 
-// Tile classes of the persistent kernel (work divisions per problem).
+// Tile classes (work divisions per problem).
 constexpr int kClsBM[kNumGroupedClasses] = {64, 64, 32};
 constexpr int kClsBN[kNumGroupedClasses] = {64, 32, 32};
 constexpr int kScaleCls = 15;  // C <- beta*C only (alpha == 0 or k == 0)
@@ -42,7 +45,7 @@ template <typename T>
 struct GTileRec {
   GemmArgs<T> g;
   int tm, tn;
-  int cls;  // class | (16-byte aligned rows: C << 4, A << 5, B << 6)
+  int cls;
   int pad;
 };
 
@@ -57,312 +60,14 @@ __device__ __forceinline__ void scale_tile(const GemmArgs<T> &g, int m0, int n0)
   }
 }
 
-// ---------------------------------------------------------------------------
-// Persistent kernel with a ring of direct global->LDS loads.
-//
-// Each workgroup walks its dealt tiles as one stream of k-steps.  A
-// load cursor runs NS-1 steps ahead of the compute cursor and fills an
-// NS-stage LDS ring with global_load_lds (4 bytes per lane, so any leading
-// dimension and any element alignment is accepted), across tile boundaries:
-// the first k-steps of the next tile arrive while the current tile finishes.
-// No staging registers are used, which leaves room for two workgroups per CU.
-//
-// Edges: rows past m and columns past n are read from clamped in-bounds
-// addresses and never stored; k past the problem's k is read from a clamped
-// address and zeroed on both operands before the multiply.
-//
-// LDS stage: A block [BM rows][128 B] (BK = 128 B of k per step), its 16-byte
-// chunks XOR-swizzled per row so that the fragment reads of 16 rows hit
-// distinct banks; B block [BK/VEC][BN][VEC]: the VEC consecutive k of one
-// column form one 16-byte chunk, so a lane reads the B values of VEC MFMAs
-// with one 16-byte load and 16 lanes read 256 contiguous bytes.
-constexpr int kGdStageA = 64 * 128;
-constexpr int kGdStageB = 8192;
-constexpr int kGdStage = kGdStageA + kGdStageB;
-constexpr int kGdNS = 3;
-constexpr int kGdMinBlocks = 3;  // workgroups per CU the register budget is sized for
-// A step issues at most 16 DMA instructions; the waits below cover the
-// steps in flight behind the one being consumed.
-static_assert((kGdNS - 2) * 16 <= 48, "ring deeper than the vmcnt waits cover");
-
-__device__ __forceinline__ int gd_bm(int cls) { return cls == 2 ? 32 : 64; }
-__device__ __forceinline__ int gd_bn(int cls) { return cls == 0 ? 64 : 32; }
-
-// Physical 16-byte chunk of logical chunk c in A row `row`.
-__device__ __forceinline__ int gd_swz_a(int row, int c) { return c ^ ((row >> 1) & 7); }
-
-template <int N>
-__device__ __forceinline__ void gd_wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
-__device__ __forceinline__ void gd_dma4(const void *src, unsigned char *lds_dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds_dst, 4, 0,
-                                   0);
-}
-
-// This lane's source addresses of one tile for every DMA slot, without the
-// k offset of the step: slot u of A covers tile row 2q + lane/32 (q = wave*ia
-// + u), slot u of B covers LDS bytes [256q, 256q + 256) of the B block.
-// Rows past m and columns past n are clamped to the last valid one.
-template <typename T>
-struct GdSlots {
-  const char *a[8];
-  const char *b[8];
-  int ia, ib;
-};
-
-// Logical k offset (elements) of 16-byte A slot u, and k row of 16-byte B
-// slot u (a 16-byte B slot covers 1 KB of the row-major block).
-template <typename T>
-__device__ __forceinline__ int gd_a16_kofs(int wave, int ia, int u, int lane) {
-  const int row = 8 * (wave * ia + u) + (lane >> 3);
-  return gd_swz_a(row, lane & 7) * (16 / (int)sizeof(T));
-}
-template <typename T>
-__device__ __forceinline__ int gd_b16_krow(int wave, int ib, int u, int lane, int bn) {
-  return ((wave * ib + u) * 1024 + lane * 16) / (bn * (int)sizeof(T));
-}
-
-// Row-major B block of a 16-byte-B tile: [BK rows][BN*size B], chunk c of
-// row r stored at gd_swz_b(r, c), which puts the rows read together by the
-// four lane groups of a fragment read (2 apart for FP64, 4 for FP32) on
-// different halves of the banks.
-template <typename T>
-__device__ __forceinline__ int gd_swz_b(int row, int c, int cpb) {  // cpb: chunks per row, >= 8
-  if (sizeof(T) == 8) return c ^ ((((row >> 1) ^ (row >> 2)) & 1) << 3);
-  return c ^ ((((row >> 2) & 3) << 2) & (cpb - 1));
-}
-
-__device__ __forceinline__ void gd_dma16(const void *src, unsigned char *lds_dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds_dst, 16, 0,
-                                   0);
-}
-
-template <typename T>
-__device__ __forceinline__ int gd_a_kofs(int wave, int ia, int u, int lane) {
-  constexpr int ESZ = sizeof(T), VEC = 16 / ESZ;
-  const int row = 2 * (wave * ia + u) + (lane >> 5);
-  return gd_swz_a(row, (lane & 31) >> 2) * VEC + ((lane & 3) * 4) / ESZ;
-}
-
-// B block byte o = ((kc*bn + col)*VEC + e)*size + (4-byte half): slot u of a
-// wave covers o in [256q, 256q + 256), q = wave*ib + u, lane at 4*lane.
-template <typename T>
-__device__ __forceinline__ int gd_b_krow(int wave, int ib, int u, int lane, int bn) {
-  constexpr int ESZ = sizeof(T), VEC = 16 / ESZ;
-  const int o = (wave * ib + u) * 256 + lane * 4;
-  return ((o >> 4) >> (bn == 64 ? 6 : 5)) * VEC + (o & 15) / ESZ;  // kc*VEC + e
-}
-
-template <typename T>
-__device__ __forceinline__ int gd_b_col(int wave, int ib, int u, int lane, int bn) {
-  const int o = (wave * ib + u) * 256 + lane * 4;
-  return (o >> 4) & (bn - 1);
-}
-
-// A16: A's rows are 16-byte aligned (pitch a multiple of 16 bytes, aligned
-// base): its slots become 16-byte loads, lane -> row 8q + lane/8, physical
-// chunk lane%8 holding logical chunk gd_swz_a(row, lane%8) -- the same LDS
-// contents as the 4-byte slots, in a quarter of the instructions.
-// 16-byte slots are built for FP64 only (kGd16 false: the FP32 kernel keeps
-// the 4-byte loads alone, which measured faster for it).
-template <typename T>
-constexpr bool kGd16 = sizeof(T) == 8;
-
-template <typename T>
-__device__ __forceinline__ void gd_setup(GdSlots<T> &sl, const GemmArgs<T> &g, int cls, int m0,
-                                         int n0, int wave, int lane, bool a16, bool b16) {
-  constexpr int ESZ = sizeof(T), VEC = 16 / ESZ;
-  a16 = kGd16<T> && a16;
-  b16 = kGd16<T> && b16;
-  const int bm = gd_bm(cls), bn = gd_bn(cls);
-  sl.ib = b16 ? bn / 32 : bn / 8;
-  const int boff = ((lane & 3) * 4) % ESZ;  // 4-byte half of an FP64 element
-  const char *A = reinterpret_cast<const char *>(g.A);
-  const char *B = reinterpret_cast<const char *>(g.B);
-  // Every slot is written on both paths (the unused 16-byte ones hold the
-  // 4-byte pointer): stores at fixed offsets keep the slot arrays in
-  // registers instead of private memory.
-  sl.ia = a16 ? bm / 32 : bm / 8;  // 16-byte: 8 rows per instruction, 4 waves
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int row4 = 2 * (wave * (bm / 8) + u) + (lane >> 5);
-    const char *p = A + ((int64_t)min(m0 + row4, g.m - 1) * g.lda +
-                         gd_a_kofs<T>(wave, bm / 8, u, lane)) * ESZ + boff;
-    if (kGd16<T> && u < 2) {
-      const int row16 = 8 * (wave * (bm / 32) + u) + (lane >> 3);
-      const char *q = A + ((int64_t)min(m0 + row16, g.m - 1) * g.lda +
-                           gd_a16_kofs<T>(wave, bm / 32, u, lane)) * ESZ;
-      p = a16 ? q : p;
-    }
-    sl.a[u] = p;
-  }
-  const int rb = bn * ESZ, last_col = ((g.n - 1) / VEC) * VEC;
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int ib4 = bn / 8;
-    const int col = gd_b_col<T>(wave, ib4, u, lane, bn);
-    const char *p = B + ((int64_t)gd_b_krow<T>(wave, ib4, u, lane, bn) * g.ldb +
-                         min(n0 + col, g.n - 1)) * ESZ + boff;
-    if (kGd16<T> && u < 2) {  // 16-byte: 1 KB (one or two k rows of the block) per instruction
-      const int o = (wave * (bn / 32) + u) * 1024 + lane * 16;
-      const int row = o / rb;
-      const int c = gd_swz_b<T>(row, (o % rb) >> 4, rb >> 4);
-      const char *q = B + ((int64_t)row * g.ldb + min(n0 + c * VEC, last_col)) * ESZ;
-      p = b16 ? q : p;
-    }
-    sl.b[u] = p;
-  }
-}
-
-// Issues this wave's share of the k-step at `kbase` (A and B blocks) into
-// `stage`; returns the number of DMA instructions issued.
-// Whole steps add one uniform offset per slot; the last, partial step of a
-// tile clamps k to the problem's last column of A / row of B.
-template <typename T>
-__device__ __forceinline__ int gd_issue(const GdSlots<T> &sl, const GemmArgs<T> &g, int cls_bits,
-                                        int kbase, unsigned char *stage, int wave, int lane) {
-  constexpr int ESZ = sizeof(T), BK = 128 / ESZ;
-  const int cls = cls_bits & 15;
-  const bool a16 = kGd16<T> && ((cls_bits >> 5) & 1), b16 = kGd16<T> && ((cls_bits >> 6) & 1);
-  const bool whole = kbase + BK <= g.k;
-  const int64_t bstep = (int64_t)kbase * g.ldb * ESZ;
-  if (a16) {
-    const int last_chunk = ((g.k - 1) / (16 / ESZ)) * (16 / ESZ);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (u < sl.ia) {
-        const char *src = sl.a[u] + (int64_t)kbase * ESZ;
-        if (!whole) {
-          const int ko = gd_a16_kofs<T>(wave, sl.ia, u, lane);
-          src = sl.a[u] + (int64_t)(min(kbase + ko, last_chunk) - ko) * ESZ;
-        }
-        gd_dma16(src, stage + (wave * sl.ia + u) * 1024);
-      }
-  }
-  if (b16) {
-    const int bn = gd_bn(cls);
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (u < sl.ib) {
-        const char *src = sl.b[u] + bstep;
-        if (!whole) {
-          const int kr = gd_b16_krow<T>(wave, sl.ib, u, lane, bn);
-          src = sl.b[u] + (int64_t)(min(kbase + kr, g.k - 1) - kr) * g.ldb * ESZ;
-        }
-        gd_dma16(src, stage + kGdStageA + (wave * sl.ib + u) * 1024);
-      }
-  }
-  if (whole) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (!a16 && u < sl.ia)
-        gd_dma4(sl.a[u] + (int64_t)kbase * ESZ, stage + (wave * sl.ia + u) * 256);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (!b16 && u < sl.ib)
-        gd_dma4(sl.b[u] + bstep, stage + kGdStageA + (wave * sl.ib + u) * 256);
-  } else {
-    const int klast = g.k - 1;
-    const int bn = gd_bn(cls);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (!a16 && u < sl.ia) {
-        const int ko = gd_a_kofs<T>(wave, sl.ia, u, lane);
-        gd_dma4(sl.a[u] + (int64_t)(min(kbase + ko, klast) - ko) * ESZ,
-                stage + (wave * sl.ia + u) * 256);
-      }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (!b16 && u < sl.ib) {
-        const int kr = gd_b_krow<T>(wave, sl.ib, u, lane, bn);
-        gd_dma4(sl.b[u] + (int64_t)(min(kbase + kr, klast) - kr) * g.ldb * ESZ,
-                stage + kGdStageA + (wave * sl.ib + u) * 256);
-      }
-  }
-  return sl.ia + sl.ib;
-}
-
-// One k-step of a BM x BN tile from an LDS stage.  TAIL: only the first
-// `kvalid` k of the step belong to the problem; the rest is zeroed on both
-// operands (values read from clamped addresses never reach the sums).
-// BROW: the step's B block is row-major (a 16-byte-B tile): one value per
-// MFMA is read instead of one 16-byte chunk of VEC k values per column.
-template <typename T, int BM, int BN, bool TAIL, bool BROW>
-__device__ __forceinline__ void gd_compute(typename Mfma<T>::acc_t (&acc)[BM / 32][BN / 32],
-                                           const unsigned char *As, const unsigned char *Bs,
-                                           int wave, int lane, int kvalid) {
-  typedef Mfma<T> M;
-  typedef typename M::vec_t V;
-  constexpr int ESZ = sizeof(T), VEC = 16 / ESZ;
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 16, FN = WN / 16;
-  const int wm0 = (wave >> 1) * WM, wn0 = (wave & 1) * WN;
-  const int g = lane >> 4, l16 = lane & 15;
-#pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int kc = 4 * r + g;
-    V a[FM];
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int row = wm0 + 16 * i + l16;
-      a[i] = *reinterpret_cast<const V *>(As + row * 128 + gd_swz_a(row, kc) * 16);
-      if (TAIL) {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) a[i][v] = kc * VEC + v < kvalid ? a[i][v] : T(0);
-      }
-    }
-    if constexpr (BROW) {
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        const int kr = kc * VEC + v;
-        T b[FN];
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int byte = (wn0 + 16 * j + l16) * ESZ;
-          b[j] = *reinterpret_cast<const T *>(
-              Bs + kr * (BN * ESZ) + gd_swz_b<T>(kr, byte >> 4, BN * ESZ / 16) * 16 + (byte & 15));
-          if (TAIL) b[j] = kr < kvalid ? b[j] : T(0);
-        }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) acc[i][j] = M::mma(a[i][v], b[j], acc[i][j]);
-      }
-    } else {
-      V b[FN];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        b[j] = *reinterpret_cast<const V *>(Bs + (kc * BN + wn0 + 16 * j + l16) * 16);
-        if (TAIL) {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) b[j][v] = kc * VEC + v < kvalid ? b[j][v] : T(0);
-        }
-      }
-#pragma unroll
-      for (int v = 0; v < VEC; ++v)
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) acc[i][j] = M::mma(a[i][v], b[j][v], acc[i][j]);
-    }
-  }
-}
-
-template <typename T, int BM, int BN>
-__device__ __forceinline__ void gd_store(const GTileRec<T> &t,
-                                         const typename Mfma<T>::acc_t (&acc)[BM / 32][BN / 32],
-                                         int wave, int lane) {
-  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 16, FN = WN / 16;
-  const int m0 = t.tm * BM + (wave >> 1) * WM, n0 = t.tn * BN + (wave & 1) * WN;
-  if ((t.cls >> 4) & 1) Epilogue<T, true>::template store<FM, FN>(t.g, acc, m0, n0, lane);
-  else Epilogue<T, false>::template store<FM, FN>(t.g, acc, m0, n0, lane);
-}
+// One workgroup per tile of the list, in list order (longest first): the
+// dispatcher hands a finished workgroup's place to the next tile, which
+// balances the CUs by the tiles' real times.  The tiles are the single-problem
+// register-staged ones, which take rows of any pitch and alignment.
+constexpr int kMinWaves = 3;  // wavefronts per SIMD: three 64x64 tiles per CU
 
 // Tile record through the constant address space: the list is never written
-// during the launch, so the uniform record loads become scalar loads, which
-// do not count against the vector-memory counter the DMA ring waits on.
+// during the launch, so the uniform record loads become scalar loads.
 template <typename T>
 __device__ __forceinline__ GTileRec<T> gd_record(const GTileRec<T> *tiles, int w) {
   typedef __attribute__((address_space(4))) const GTileRec<T> CRec;
@@ -371,180 +76,33 @@ __device__ __forceinline__ GTileRec<T> gd_record(const GTileRec<T> *tiles, int w
   return r;
 }
 
-// Load cursor of a workgroup: walks the same tiles as the compute side,
-// NS-1 k-steps ahead, and remembers how many DMA instructions each issued
-// but unconsumed step has (NS-1 of them).
-// Tile of workgroup b in dealing round r: rounds alternate direction
-// (b', then G-1-b'), so with the list in decreasing cost every workgroup gets
-// a fair share of the expensive and of the cheap tiles.  b' numbers the
-// workgroups XCD by XCD (the dispatcher places workgroup b on XCD b % 8), so
-// each XCD takes a contiguous run of every round: the tiles of one problem,
-// adjacent in the list, then share one L2.  Past the list: ntiles.
-__device__ __forceinline__ int gd_deal(int r, int b, int G, int ntiles) {
-  if ((int64_t)r * G >= ntiles) return ntiles;
-  const int bx = xcd_remap(b, G);
-  const int w = r * G + ((r & 1) ? G - 1 - bx : bx);
-  return w < ntiles ? w : ntiles;
+// Tile of workgroup b: the list is dealt in rounds of `round` tiles (the
+// workgroups resident at once), and within a round each XCD takes a
+// contiguous run (the dispatcher places workgroup b on XCD b % 8): the tiles
+// of one problem, adjacent in the list, then share one L2.
+__device__ __forceinline__ int gd_deal(int b, int round, int ntiles) {
+  const int first = b / round * round;
+  return first + xcd_remap(b - first, min(round, ntiles - first));
 }
 
 template <typename T>
-struct GdLoader {
-  const GTileRec<T> *tiles;
-  int ntiles, G, lr, lw, lkt, li;
-  GTileRec<T> L;
-  GdSlots<T> sl;
-  unsigned char *lds;
-  int wave, lane;
-  int q[kGdNS - 1];  // DMA counts of the issued, unconsumed steps, oldest first (0: none)
-
-  // DMA instructions issued after the oldest unconsumed step.
-  __device__ __forceinline__ int later() const {
-    int n = 0;
-#pragma unroll
-    for (int i = 1; i < kGdNS - 1; ++i) n += q[i];
-    return n;
-  }
-  // The oldest step was consumed; `cnt` is the step just issued.
-  __device__ __forceinline__ void push(int cnt) {
-#pragma unroll
-    for (int i = 0; i < kGdNS - 2; ++i) q[i] = q[i + 1];
-    q[kGdNS - 2] = cnt;
-  }
-
-  __device__ __forceinline__ void next_tile() {
-    do {
-      lw = gd_deal(++lr, (int)blockIdx.x, G, ntiles);
-      if (lw < ntiles) L = gd_record(tiles, lw);
-    } while (lw < ntiles && (L.cls & 15) == kScaleCls);
-    if (lw < ntiles) {
-      const int c = L.cls & 15;
-      gd_setup<T>(sl, L.g, c, L.tm * gd_bm(c), L.tn * gd_bn(c), wave, lane, (L.cls >> 5) & 1,
-                  (L.cls >> 6) & 1);
-    }
-  }
-  // Issues the next k-step of the stream; returns its DMA count (0 if none).
-  __device__ __forceinline__ int issue() {
-    constexpr int BK = 128 / (int)sizeof(T);
-    if (lw >= ntiles) return 0;
-    const int cnt = gd_issue<T>(sl, L.g, L.cls, lkt * BK, lds + (li % kGdNS) * kGdStage,
-                                wave, lane);
-    ++li;
-    if (++lkt * BK >= L.g.k) {
-      lkt = 0;
-      next_tile();
-    }
-    return cnt;
-  }
-};
-
-// Waits until at most `n` (the DMA instructions of the steps issued after
-// the current one) vector memory operations of this wave are outstanding:
-// the current step has landed.  DMA instructions per step: A 8 / 4
-// (4-byte, 64 / 32 rows) or 2 / 1 (16-byte) plus B 8 / 4 (4-byte, 64 / 32
-// columns) or 2 / 1 (16-byte).
-#define MG_GD_W1(N) \
-  case N: gd_wait_vmcnt<N>(); break;
-#define MG_GD_W4(N) MG_GD_W1(N) MG_GD_W1(N + 1) MG_GD_W1(N + 2) MG_GD_W1(N + 3)
-#define MG_GD_W16(N) MG_GD_W4(N) MG_GD_W4(N + 4) MG_GD_W4(N + 8) MG_GD_W4(N + 12)
-__device__ __forceinline__ void gd_wait_next(int n) {
-  if constexpr (kGdNS <= 3) {  // one step behind the current one: at most 16
-    switch (n) {  // the step counts that occur (a sum of one A and one B count)
-      MG_GD_W1(16) MG_GD_W1(12) MG_GD_W1(10) MG_GD_W1(9) MG_GD_W1(8)
-      MG_GD_W1(6) MG_GD_W1(5) MG_GD_W1(4) MG_GD_W1(3) MG_GD_W1(2)
-      default: gd_wait_vmcnt<0>(); break;  // 0: wait for all
-    }
-  } else {
-    switch (n) {
-      MG_GD_W16(1)
-      MG_GD_W16(17)
-      MG_GD_W16(33)
-      default: gd_wait_vmcnt<0>(); break;  // 0, or past the covered range: wait for all
-    }
-  }
-}
-#undef MG_GD_W16
-#undef MG_GD_W4
-#undef MG_GD_W1
-
-// All k-steps of one tile of class (BM, BN), then its epilogue; `t` counts
-// the workgroup's consumed steps (ring position).
-template <typename T, int BM, int BN>
-__device__ __forceinline__ void gd_run_tile(GdLoader<T> &ld, const GTileRec<T> &C, int &t) {
-  typedef typename Mfma<T>::acc_t Acc;
-  constexpr int BK = 128 / (int)sizeof(T);
-  constexpr int FM = BM / 32, FN = BN / 32;
-  Acc acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = Acc{};
-  const int KT = (C.g.k + BK - 1) / BK;
-  const bool brow = kGd16<T> && ((C.cls >> 6) & 1);
-  for (int kt = 0; kt < KT; ++kt) {
-    gd_wait_next(ld.later());
-    __builtin_amdgcn_s_barrier();
-    // the stage the loader refills next (consumed in the previous step)
-    MG_LDS_POISON_STAGE(ld.lds + (ld.li % kGdNS) * kGdStage, kGdStage);
-    // The ring's refill is issued at raised priority: the waves of the other
-    // workgroups on this SIMD are mostly issuing MFMAs, and a refill held
-    // behind them shortens the ring's lead (FP64 batch of 2000 problems:
-    // 0.617 -> 0.58 ms; FP32 unchanged).
-    __builtin_amdgcn_s_setprio(2);
-    const int cnew = ld.issue();
-    __builtin_amdgcn_s_setprio(0);
-    const unsigned char *As = ld.lds + (t % kGdNS) * kGdStage;
-    const unsigned char *Bs = As + kGdStageA;
-    const int kvalid = C.g.k - kt * BK;
-    if (brow) {  // always false for FP32: the row-major path is not built there
-      if constexpr (kGd16<T>) {
-        if (kvalid >= BK) gd_compute<T, BM, BN, false, true>(acc, As, Bs, ld.wave, ld.lane, kvalid);
-        else gd_compute<T, BM, BN, true, true>(acc, As, Bs, ld.wave, ld.lane, kvalid);
-      }
-    } else {
-      if (kvalid >= BK) gd_compute<T, BM, BN, false, false>(acc, As, Bs, ld.wave, ld.lane, kvalid);
-      else gd_compute<T, BM, BN, true, false>(acc, As, Bs, ld.wave, ld.lane, kvalid);
-    }
-    ld.push(cnew);
-    ++t;
-  }
-  gd_store<T, BM, BN>(C, acc, ld.wave, ld.lane);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kTileThreads, kGdMinBlocks) void grouped_dma_kernel(
-    const GTileRec<T> *__restrict__ tiles, int ntiles) {
+__global__ __launch_bounds__(kTileThreads, kMinWaves) void grouped_kernel(
+    const GTileRec<T> *__restrict__ tiles, int ntiles, int round) {
   extern __shared__ __align__(16) unsigned char lds[];
-  GdLoader<T> ld;
-  ld.tiles = tiles;
-  ld.ntiles = ntiles;
-  ld.G = (int)gridDim.x;
-  ld.lds = lds;
-  // wave index made uniform so LDS destinations (M0) are scalar arithmetic
-  ld.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  ld.lane = threadIdx.x & 63;
-  ld.lkt = 0;
-  ld.li = 0;
-  ld.lr = -1;
-  MG_LDS_POISON_STAGE(lds, kGdNS * kGdStage);
-  ld.next_tile();  // first tile with k-steps
-#pragma unroll
-  for (int i = 0; i < kGdNS - 1; ++i) ld.q[i] = ld.issue();
-
-  int cr = 0, t = 0;
-  for (int cw = gd_deal(0, blockIdx.x, ld.G, ntiles); cw < ntiles;
-       cw = gd_deal(++cr, blockIdx.x, ld.G, ntiles)) {
-    const GTileRec<T> C = gd_record(tiles, cw);
-    const int c = C.cls & 15;
-    if (c == kScaleCls) scale_tile<T>(C.g, C.tm * kScaleTile, C.tn * kScaleTile);
-    else if (c == 0) gd_run_tile<T, 64, 64>(ld, C, t);
-    else if (c == 1) gd_run_tile<T, 64, 32>(ld, C, t);
-    else gd_run_tile<T, 32, 32>(ld, C, t);
-  }
+  T *smem = reinterpret_cast<T *>(lds);
+  const GTileRec<T> r = gd_record(tiles, gd_deal(blockIdx.x, round, ntiles));
+  // Wavefronts of ragged tiles that lie past the matrix skip the products;
+  // turning the tile's parts over the wavefronts spreads them over the SIMDs.
+  const int turn = (blockIdx.x >> 3) & 3;
+  if (r.cls == kScaleCls) scale_tile<T>(r.g, r.tm * kScaleTile, r.tn * kScaleTile);
+  else if (r.cls == 0) gemm_tile<T, 64, 64>(r.g, r.tm * 64, r.tn * 64, smem, turn);
+  else if (r.cls == 1) gemm_tile<T, 64, 32>(r.g, r.tm * 64, r.tn * 32, smem, turn);
+  else gemm_tile<T, 32, 32>(r.g, r.tm * 32, r.tn * 32, smem, turn);
 }
 
 template <typename T>
-size_t grouped_lds_bytes() {
-  return (size_t)kGdNS * kGdStage;
+constexpr size_t grouped_lds_bytes() {
+  return TileShape<T, 64, 64>::LDS_BYTES;  // the largest class
 }
 
 int bucket_of(int64_t x) {
@@ -572,15 +130,42 @@ int grouped_class_tile(int cls, int *bm, int *bn) {
   return MG_OK;
 }
 
-// Heuristic class when no tuning table is given: the largest tile that does
-// not waste more than a quarter of its area on padding.
-int heuristic_class(int64_t m, int64_t n) {
+// Class when no tuning table is given: the least count of
+//   tiles x (per tile + per k-step x k-steps),
+// the microseconds of one CU a tile takes in a full batch, fitted to batches
+// forced to each class (2000 problems of extents 16-512, 500 of 64-128, 1000
+// of 16-64 and 100 of 128-512; 6 % off on average).  Per tile: the launch, the
+// first loads' latency and C; per k-step: the products and the panels' loads,
+// so padding counts by what it costs.  The largest tile wasting at most a
+// quarter of its area, the rule before, took 467 / 280 us (FP64 / FP32) for the
+// 2000 problems where this takes 411 / 241.
+struct ClassCost {
+  double tile, step;
+};
+constexpr ClassCost kCost64[kNumGroupedClasses] = {{2.6, 0.52}, {1.5, 0.29}, {1.2, 0.15}};
+constexpr ClassCost kCost32[kNumGroupedClasses] = {{0.9, 0.70}, {0.95, 0.31}, {0.9, 0.162}};
+
+namespace {
+
+double tile_cost(int dtype, int cls, int64_t k) {
+  const ClassCost &c = dtype == MG_F64 ? kCost64[cls] : kCost32[cls];
+  return c.tile + c.step * (double)ceil_div(k, dtype == MG_F64 ? 16 : 32);
+}
+
+}  // namespace
+
+int heuristic_class(int dtype, int64_t m, int64_t n, int64_t k) {
+  int best = 0;
+  double least = 0;
   for (int c = 0; c < kNumGroupedClasses; ++c) {
-    const double used = (double)(m * n);
-    const double padded = (double)(round_up(m, kClsBM[c]) * round_up(n, kClsBN[c]));
-    if (used >= 0.75 * padded) return c;
+    const double cost =
+        (double)(ceil_div(m, kClsBM[c]) * ceil_div(n, kClsBN[c])) * tile_cost(dtype, c, k);
+    if (c == 0 || cost < least) {
+      best = c;
+      least = cost;
+    }
   }
-  return kNumGroupedClasses - 1;
+  return best;
 }
 
 struct Plan {
@@ -599,6 +184,7 @@ namespace {
 
 template <typename T>
 int build_t(int64_t count, const mg_problem *probs, const mg_tune_table *table, WorkList *out) {
+  constexpr int dtype = std::is_same<T, double>::value ? MG_F64 : MG_F32;
   std::vector<GemmArgs<T>> hp((size_t)count);
   std::vector<GTileRec<T>> tiles;
   std::vector<double> cost;
@@ -624,29 +210,20 @@ int build_t(int64_t count, const mg_problem *probs, const mg_tune_table *table, 
       for (int a = 0; a < tm; ++a)
         for (int b = 0; b < tn; ++b) {
           tiles.push_back(GTileRec<T>{g, a, b, kScaleCls, 0});
-          cost.push_back((double)kScaleTile * kScaleTile);
+          cost.push_back(0.5);  // C alone
         }
       per_cls[kNumGroupedClasses] += (int64_t)tm * tn;
       bytes += (double)q.m * q.n * sizeof(T) * (q.beta != 0.0 ? 2 : 1);
       continue;
     }
-    int cls = table ? table->cls[tune_bucket(q.m, q.n, q.k)] : heuristic_class(q.m, q.n);
-    if (cls < 0 || cls >= kNumGroupedClasses) cls = heuristic_class(q.m, q.n);
-    const bool c_vec = vec_aligned(q.C, q.ldc, sizeof(T), Mfma<T>::VEC);
-    const bool a_vec = vec_aligned(q.A, q.lda, sizeof(T), Mfma<T>::VEC);
-    // 16-byte B loads (row-major B block) for FP64 only: FP32 reads that
-    // layout one value per MFMA, four per 16-byte chunk, which measured
-    // slower than its 4-byte loads into the k-interleaved block.
-    const bool b_vec = sizeof(T) == 8 && vec_aligned(q.B, q.ldb, sizeof(T), Mfma<T>::VEC);
+    int cls = table ? table->cls[tune_bucket(q.m, q.n, q.k)] : -1;
+    if (cls < 0 || cls >= kNumGroupedClasses) cls = heuristic_class(dtype, q.m, q.n, q.k);
     const int bm = kClsBM[cls], bn = kClsBN[cls];
     const int tm = (int)ceil_div(q.m, bm), tn = (int)ceil_div(q.n, bn);
     for (int a = 0; a < tm; ++a)
       for (int b = 0; b < tn; ++b) {
-        tiles.push_back(
-            GTileRec<T>{g, a, b, cls | (c_vec ? 16 : 0) | (a_vec ? 32 : 0) | (b_vec ? 64 : 0), 0});
-        // MFMA work of the padded tile plus its operand traffic (in FLOP-equivalents)
-        cost.push_back(2.0 * bm * bn * (double)round_up(q.k, Mfma<T>::BK) +
-                       16.0 * (bm + bn) * (double)q.k);
+        tiles.push_back(GTileRec<T>{g, a, b, cls, 0});
+        cost.push_back(tile_cost(dtype, cls, q.k));
       }
     per_cls[cls] += (int64_t)tm * tn;
     flops += 2.0 * q.m * q.n * q.k;
@@ -657,12 +234,12 @@ int build_t(int64_t count, const mg_problem *probs, const mg_tune_table *table, 
     set_error("too many tiles");
     return MG_ERR_INVALID_ARG;
   }
-  // Longest-processing-time order: dealt round-robin to the workgroups, the
-  // expensive tiles spread evenly and the cheap ones fill in at the end.
+  // Longest first: the expensive tiles start at once and the cheap ones fill
+  // in at the end.
   std::vector<int> order(tiles.size());
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-  out->dtype = std::is_same<T, double>::value ? MG_F64 : MG_F32;
+  out->dtype = dtype;
   out->tiles.resize(tiles.size() * sizeof(GTileRec<T>));
   GTileRec<T> *dst = reinterpret_cast<GTileRec<T> *>(out->tiles.data());
   for (size_t i = 0; i < order.size(); ++i) dst[i] = tiles[(size_t)order[i]];
@@ -695,12 +272,12 @@ int occupancy_t(int *cus, int *occ) {
     else if ((r.err = hipDeviceGetAttribute(&r.cus, hipDeviceAttributeMultiprocessorCount, dev)) !=
              hipSuccess)
       r.what = "hipDeviceGetAttribute";
-    else if ((r.err = hipFuncSetAttribute(reinterpret_cast<const void *>(grouped_dma_kernel<T>),
+    else if ((r.err = hipFuncSetAttribute(reinterpret_cast<const void *>(grouped_kernel<T>),
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)) !=
              hipSuccess)
       r.what = "hipFuncSetAttribute";
     else if ((r.err = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                  &r.occ, reinterpret_cast<const void *>(grouped_dma_kernel<T>), kTileThreads,
+                  &r.occ, reinterpret_cast<const void *>(grouped_kernel<T>), kTileThreads,
                   lds)) != hipSuccess)
       r.what = "hipOccupancyMaxActiveBlocksPerMultiprocessor";
     r.occ = std::max(1, r.occ);
@@ -717,8 +294,8 @@ int occupancy_t(int *cus, int *occ) {
 
 template <typename T>
 int launch_t(const void *d_tiles, int ntiles, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(grouped_dma_kernel<T>, dim3(grid), dim3(kTileThreads), grouped_lds_bytes<T>(), s,
-                     static_cast<const GTileRec<T> *>(d_tiles), ntiles);
+  hipLaunchKernelGGL(grouped_kernel<T>, dim3(ntiles), dim3(kTileThreads), grouped_lds_bytes<T>(), s,
+                     static_cast<const GTileRec<T> *>(d_tiles), ntiles, grid);
   MG_HIP_TRY(hipGetLastError());
   return MG_OK;
 }
@@ -783,7 +360,7 @@ int plan_launch(Plan *p, hipStream_t s, bool use_graph) {
   if (p->ntiles == 0) return MG_OK;
   if (!use_graph) return launch_raw(p, s);
   if (p->exec == nullptr) {
-    // Capture the persistent launch once on a private stream.
+    // Capture the launch once on a private stream.
     hipStream_t cap;
     MG_HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
@@ -985,7 +562,7 @@ int autotune(int dtype, int reps, hipStream_t s, mg_tune_table *out) {
           ob += b_sz;
         }
         float best = 0;
-        int best_cls = heuristic_class(m, n);
+        int best_cls = heuristic_class(dtype, m, n, k);
         for (int c = 0; c < kNumGroupedClasses && rc == MG_OK; ++c) {
           forced.dtype = dtype;
           for (int b = 0; b < MG_TUNE_BUCKETS; ++b) forced.cls[b] = c;

@@ -4,7 +4,7 @@
 // 216 shape buckets a previous process already timed on the same part.
 //
 //   {"format": "mg-autotune-1", "tables": [
-//   {"arch": "gfx950:sramecc+:xnack-", "cus": 256, "dtype": "f64", "lib": 10100, "classes": [...]},
+//   {"arch": "gfx950:sramecc+:xnack-", "cus": 256, "dtype": "f64", "lib": 10200, "classes": [...]},
 //   ...
 //   ]}
 //
