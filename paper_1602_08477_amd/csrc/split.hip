@@ -33,6 +33,13 @@ namespace {
 constexpr int kStageBytes = 128;  // k bytes of one slice row per LDS stage
 constexpr int kPitch = kStageBytes + 16;  // LDS row pitch: conflict-free b128 reads
 
+// A pointer read from memory, known to be global (flat loads and stores also
+// wait on the LDS counter).
+template <typename T>
+__device__ __forceinline__ T *in_global(T *p) {
+  return (T *)(__attribute__((address_space(1))) T *)(unsigned long long)p;
+}
+
 __device__ __forceinline__ int exp_of(double x) {
   if (x == 0.0) return INT_MIN;
   int e;
@@ -116,6 +123,85 @@ __device__ __forceinline__ void slice_round(double *r, int *q, int bits) {
   }
 }
 
+// The slices of the default counts (7 of 7 bits, 6 of 8) as digits: |x| 2^-e
+// is truncated to a fixed-point number of S*BITS bits, held in two words and
+// cut into S digits with x's sign.  slice_round gives the same integers (its
+// remainders are exact), in 4 double-precision instructions per slice instead
+// of 6 for all of them.
+template <int ESZ>
+struct Digits {
+  static constexpr int S = ESZ == 2 ? 6 : 7, BITS = ESZ == 2 ? 8 : 7;
+  static constexpr int LO = (S - 3) * BITS;  // digits 4..S in `lo`, 1..3 in `hi`
+  static_assert(3 * BITS < 32 && LO < 32, "a digit lies in one word");
+  unsigned hi, lo;
+  int sign;
+  __device__ __forceinline__ void set(double x, int e) {
+    const double y = trunc(ldexp(fabs(x), S * BITS - e));
+    hi = (unsigned)(y * (1.0 / (double)(1u << LO)));
+    lo = (unsigned)fma((double)hi, -(double)(1u << LO), y);
+    sign = x < 0.0 ? -1 : 0;
+  }
+  __device__ __forceinline__ int get(int t) const {  // t = 0 .. S-1
+    const unsigned d = t < 3 ? hi >> ((2 - t) * BITS) : lo >> ((S - 1 - t) * BITS);
+    return ((int)(d & ((1u << BITS) - 1)) ^ sign) - sign;
+  }
+};
+
+// Stores a thread's 4 consecutive k of a row of A: all s slices.
+template <int ESZ>
+__device__ __forceinline__ void store_quad(const int (&q)[4], unsigned char *o) {
+  if (ESZ == 1) {
+    const unsigned w = (q[0] & 0xff) | ((q[1] & 0xff) << 8) | ((q[2] & 0xff) << 16) |
+                       ((unsigned)(q[3] & 0xff) << 24);
+    *reinterpret_cast<unsigned *>(o) = w;
+  } else {
+    uint2 w;
+    w.x = SlicePack<2>::bf16_bits(q[0]) | (SlicePack<2>::bf16_bits(q[1]) << 16);
+    w.y = SlicePack<2>::bf16_bits(q[2]) | (SlicePack<2>::bf16_bits(q[3]) << 16);
+    *reinterpret_cast<uint2 *>(o) = w;
+  }
+}
+
+template <int ESZ>
+__device__ __forceinline__ void slice_quad(const double (&x)[4], int e, int s, int bits,
+                                           int64_t slice_bytes, unsigned char *o) {
+  int q[4];
+  if (s == Digits<ESZ>::S) {
+    Digits<ESZ> d[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) d[v].set(x[v], e);
+#pragma unroll
+    for (int t = 0; t < Digits<ESZ>::S; ++t) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) q[v] = d[v].get(t);
+      store_quad<ESZ>(q, o + t * slice_bytes);
+    }
+    return;
+  }
+  double r[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) r[v] = ldexp(x[v], -e);
+  for (int t = 0; t < s; ++t) {
+    slice_round<4>(r, q, bits);
+    store_quad<ESZ>(q, o + t * slice_bytes);
+  }
+}
+
+// 4 consecutive values of a row (k long) from kk on; 0 past its end.  Two wide
+// loads at any 8-byte alignment (four conditional ones before, with the digits
+// above 225 -> 211 us for the 2000-problem INT8 batch, 81 -> 75 us at n = 4096).
+__device__ __forceinline__ void load_quad(const double *row, int kk, int k, double (&x)[4]) {
+  typedef double quad __attribute__((ext_vector_type(4), aligned(8)));
+  if (kk + 4 <= k) {
+    const quad v = *reinterpret_cast<const quad *>(row + kk);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = v[e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = kk + e < k ? row[kk + e] : 0.0;
+  }
+}
+
 // Steps 1 and 2 for A in one pass: one workgroup per (padded) row finds the
 // row's exponent and slices it, so A is read from HBM once.  A thread owns
 // quads (4 consecutive k) tid, tid+256, ...; rows up to 4096 long stay in
@@ -130,20 +216,16 @@ __device__ __forceinline__ void slice_rows_exp_body(const double *A, int64_t lda
   const double *row = A + (int64_t)(live ? i : 0) * lda;
   const int64_t quads = kp / 4;
   const bool regs = quads <= 256 * QPT;
-  auto load = [&](int64_t kk) { return (live && kk < k) ? row[kk] : 0.0; };
+  const int lim = live ? k : 0;
   double x[QPT][4];
   int e = INT_MIN;
   for (int64_t q0 = 0; q0 < quads; q0 += 256 * QPT) {
 #pragma unroll
-    for (int j = 0; j < QPT; ++j) {
-      const int64_t qd = q0 + tid + 256 * j;
+    for (int j = 0; j < QPT; ++j) load_quad(row, (int)(q0 + tid + 256 * j) * 4, lim, x[j]);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const double val = qd < quads ? load(qd * 4 + v) : 0.0;
-        x[j][v] = val;
-        e = max(e, exp_of(val));
-      }
-    }
+    for (int j = 0; j < QPT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) e = max(e, exp_of(x[j][v]));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
@@ -155,28 +237,15 @@ __device__ __forceinline__ void slice_rows_exp_body(const double *A, int64_t lda
   if (tid == 0) E[i] = ei;
   const int64_t slice_bytes = (int64_t)mp * kp * ESZ;
   for (int64_t q0 = 0; q0 < quads; q0 += 256 * QPT) {
+    if (!regs) {
+#pragma unroll
+      for (int j = 0; j < QPT; ++j) load_quad(row, (int)(q0 + tid + 256 * j) * 4, lim, x[j]);
+    }
 #pragma unroll
     for (int j = 0; j < QPT; ++j) {
       const int64_t qd = q0 + tid + 256 * j;
       if (qd >= quads) continue;
-      double r[4];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) r[v] = ldexp(regs ? x[j][v] : load(qd * 4 + v), -ei);
-      unsigned char *o = out + ((int64_t)i * kp + qd * 4) * ESZ;
-      for (int t = 0; t < s; ++t) {
-        int q[4];
-        slice_round<4>(r, q, bits);
-        if (ESZ == 1) {
-          const unsigned w = (q[0] & 0xff) | ((q[1] & 0xff) << 8) | ((q[2] & 0xff) << 16) |
-                             ((unsigned)(q[3] & 0xff) << 24);
-          *reinterpret_cast<unsigned *>(o + t * slice_bytes) = w;
-        } else {
-          uint2 w;
-          w.x = SlicePack<2>::bf16_bits(q[0]) | (SlicePack<2>::bf16_bits(q[1]) << 16);
-          w.y = SlicePack<2>::bf16_bits(q[2]) | (SlicePack<2>::bf16_bits(q[3]) << 16);
-          *reinterpret_cast<uint2 *>(o + t * slice_bytes) = w;
-        }
-      }
+      slice_quad<ESZ>(x[j], ei, s, bits, slice_bytes, out + ((int64_t)i * kp + qd * 4) * ESZ);
     }
   }
 }
@@ -199,16 +268,11 @@ __device__ __forceinline__ void slice_rows_wave_body(const double *A, int64_t ld
   double x[QPT][4];
   int e = INT_MIN;
 #pragma unroll
-  for (int j = 0; j < QPT; ++j) {
-    const int qd = lane + LPR * j;
+  for (int j = 0; j < QPT; ++j) load_quad(row, (lane + LPR * j) * 4, live ? k : 0, x[j]);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int kk = qd * 4 + v;
-      const double val = (live && qd < quads && kk < k) ? row[kk] : 0.0;
-      x[j][v] = val;
-      e = max(e, exp_of(val));
-    }
-  }
+  for (int j = 0; j < QPT; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) e = max(e, exp_of(x[j][v]));
 #pragma unroll
   for (int off = LPR / 2; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
   const int ei = (e == INT_MIN) ? 0 : e;
@@ -218,24 +282,7 @@ __device__ __forceinline__ void slice_rows_wave_body(const double *A, int64_t ld
   for (int j = 0; j < QPT; ++j) {
     const int qd = lane + LPR * j;
     if (qd >= quads) continue;
-    double r[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) r[v] = ldexp(x[j][v], -ei);
-    unsigned char *o = out + ((int64_t)i * kp + qd * 4) * ESZ;
-    for (int t = 0; t < s; ++t) {
-      int q[4];
-      slice_round<4>(r, q, bits);
-      if (ESZ == 1) {
-        const unsigned w = (q[0] & 0xff) | ((q[1] & 0xff) << 8) | ((q[2] & 0xff) << 16) |
-                           ((unsigned)(q[3] & 0xff) << 24);
-        *reinterpret_cast<unsigned *>(o + t * slice_bytes) = w;
-      } else {
-        uint2 w;
-        w.x = SlicePack<2>::bf16_bits(q[0]) | (SlicePack<2>::bf16_bits(q[1]) << 16);
-        w.y = SlicePack<2>::bf16_bits(q[2]) | (SlicePack<2>::bf16_bits(q[3]) << 16);
-        *reinterpret_cast<uint2 *>(o + t * slice_bytes) = w;
-      }
-    }
+    slice_quad<ESZ>(x[j], ei, s, bits, slice_bytes, out + ((int64_t)i * kp + qd * 4) * ESZ);
   }
 }
 
@@ -265,39 +312,64 @@ __device__ __forceinline__ void slice_cols_body(const double *B, int64_t ldb, in
   // of 64 columns, 25 % slower in the 2000-problem batch; rotating T's
   // columns per 16-row block left the conflict count unchanged.)
   __shared__ double T[64][65];
-  const int64_t kblocks = kp / 64;
-  const int j0 = (int)(block / kblocks) * 64;
-  const int64_t k0 = (block % kblocks) * 64;
+  const int kblocks = (int)(kp / 64);
+  const int j0 = block / kblocks * 64;
+  const int k0 = block % kblocks * 64;
   const int tid = threadIdx.x;
-  for (int e = tid; e < 64 * 64; e += 256) {
-    const int kk = e >> 6, jj = e & 63;
-    const int64_t gk = k0 + kk;
-    const int gj = j0 + jj;
-    T[kk][jj] = (gk < k && gj < n) ? B[gk * ldb + gj] : 0.0;
+  // F[j] still holds INT_MIN for an all-zero (or padding) column: its scale
+  // is 0, and the first k-block of the column stores that back for the
+  // product kernel's epilogue.
+  const int fraw = F[j0 + (tid >> 2)];
+  // Bound by memory latency before, by bandwidth now: all 16 loads of a thread
+  // are in flight together, from addresses clamped into B.  With one load
+  // under a condition per pass of a loop each was waited for: 282 -> 160 us
+  // for B's slices in the 2000-problem INT8 batch, 90 -> 66 us at n = 4096.
+  {
+    const int j = j0 + (tid & 63), gk = k0 + (tid >> 6);
+    double v[16];
+    if (k > 0 && n > 0) {
+      const double *col = B + min(j, n - 1);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = col[min(gk + 4 * u, k - 1) * ldb];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      T[(tid >> 6) + 4 * u][tid & 63] = gk + 4 * u < k && j < n ? v[u] : 0.0;
   }
   __syncthreads();
   // column jj, 16-long k range kq: the 4 lanes of a column write its 64
   // contiguous bytes of each slice
   const int jj = tid >> 2, kq = tid & 3;
   const int j = j0 + jj;
-  // F[j] still holds INT_MIN for an all-zero (or padding) column: its scale
-  // is 0, and the first k-block of the column stores that back for the
-  // product kernel's epilogue.
-  const int fraw = F[j];
   const int fj = fraw == INT_MIN ? 0 : fraw;
   if (k0 == 0 && kq == 0 && fraw == INT_MIN) F[j] = 0;
-  double r[16];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) r[e] = ldexp(T[kq * 16 + e][jj], -fj);
   constexpr int CW = SlicePack<ESZ>::CW;
   const int64_t slice_bytes = (int64_t)np * kp * ESZ;
   unsigned char *o = out + ((int64_t)j * kp + k0 + kq * 16) * ESZ;
-  for (int t = 0; t < s; ++t) {
-    int q[16];
-    slice_round<16>(r, q, bits);
+  int q[16];
+  auto store = [&](int t) {
 #pragma unroll
     for (int h = 0; h < 16 / CW; ++h)
       *reinterpret_cast<i4v *>(o + t * slice_bytes + h * 16) = SlicePack<ESZ>::pack(q + h * CW);
+  };
+  if (s == Digits<ESZ>::S) {
+    Digits<ESZ> d[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) d[e].set(T[kq * 16 + e][jj], fj);
+#pragma unroll
+    for (int t = 0; t < Digits<ESZ>::S; ++t) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) q[e] = d[e].get(t);
+      store(t);
+    }
+    return;
+  }
+  double r[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) r[e] = ldexp(T[kq * 16 + e][jj], -fj);
+  for (int t = 0; t < s; ++t) {
+    slice_round<16>(r, q, bits);
+    store(t);
   }
 }
 
@@ -1155,33 +1227,39 @@ __global__ __launch_bounds__(256) void batched_fill_kernel(const SplitPrepDesc *
 // block finds the exponent of one row of A and slices it.
 template <int ESZ>
 __global__ __launch_bounds__(256) void batched_exp_rows_kernel(const SplitPrepDesc *d,
-                                                               const int *first, int count,
-                                                               int s, int bits) {
+                                                               const int *first, int count) {
+  constexpr int S = Digits<ESZ>::S, BITS = Digits<ESZ>::BITS;
   const int i = batch_problem(first, count, blockIdx.x);
   const SplitPrepDesc &q = d[i];
   const int lb = blockIdx.x - first[i], ncol = q.cx * q.cy;
-  if (lb < ncol)
-    col_exp_body(q.B, q.ldb, q.k, q.n, q.F, lb % q.cx, lb / q.cx, q.cy);
-  else if (q.rpb == 1)
-    slice_rows_exp_body<ESZ>(q.A, q.lda, q.m, q.k, q.mp, q.kp, q.E, s, bits, q.As, lb - ncol);
+  if (lb < ncol) {
+    col_exp_body(in_global(q.B), q.ldb, q.k, q.n, in_global(q.F), lb % q.cx, lb / q.cx, q.cy);
+    return;
+  }
+  const double *A = in_global(q.A);
+  int *E = in_global(q.E);
+  unsigned char *As = in_global(q.As);
+  const int b = lb - ncol, tid = threadIdx.x;
+  if (q.rpb == 1)
+    slice_rows_exp_body<ESZ>(A, q.lda, q.m, q.k, q.mp, q.kp, E, S, BITS, As, b);
   else if (q.rpb == 16)
-    slice_rows_wave_body<ESZ, 16>(q.A, q.lda, q.m, q.k, q.mp, q.kp, q.E, s, bits, q.As,
-                                  (lb - ncol) * 16 + (int)(threadIdx.x >> 4));
+    slice_rows_wave_body<ESZ, 16>(A, q.lda, q.m, q.k, q.mp, q.kp, E, S, BITS, As,
+                                  b * 16 + (tid >> 4));
   else if (q.rpb == 8)
-    slice_rows_wave_body<ESZ, 32>(q.A, q.lda, q.m, q.k, q.mp, q.kp, q.E, s, bits, q.As,
-                                  (lb - ncol) * 8 + (int)(threadIdx.x >> 5));
+    slice_rows_wave_body<ESZ, 32>(A, q.lda, q.m, q.k, q.mp, q.kp, E, S, BITS, As,
+                                  b * 8 + (tid >> 5));
   else
-    slice_rows_wave_body<ESZ, 64>(q.A, q.lda, q.m, q.k, q.mp, q.kp, q.E, s, bits, q.As,
-                                  (lb - ncol) * 4 + (int)(threadIdx.x >> 6));
+    slice_rows_wave_body<ESZ, 64>(A, q.lda, q.m, q.k, q.mp, q.kp, E, S, BITS, As,
+                                  b * 4 + (tid >> 6));
 }
 
 template <int ESZ>
 __global__ __launch_bounds__(256) void batched_slice_cols_kernel(const SplitPrepDesc *d,
-                                                                 const int *first, int count,
-                                                                 int s, int bits) {
+                                                                 const int *first, int count) {
   const int i = batch_problem(first, count, blockIdx.x);
   const SplitPrepDesc &q = d[i];
-  slice_cols_body<ESZ>(q.B, q.ldb, q.k, q.n, q.np, q.kp, q.F, s, bits, q.Bs,
+  slice_cols_body<ESZ>(in_global(q.B), q.ldb, q.k, q.n, q.np, q.kp, in_global(q.F),
+                       Digits<ESZ>::S, Digits<ESZ>::BITS, in_global(q.Bs),
                        blockIdx.x - first[i]);
 }
 
@@ -1395,16 +1473,15 @@ int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const
                      hipStream_t s) {
   constexpr int ESZ = ALGO == MG_SPLIT_BF16 ? 2 : 1;
   constexpr int S = batch_slices(ALGO);
-  const int bits = split_bits(ALGO);
   typedef AllPairsShape<S, kAllPairsNS> SH;
   static int once = ensure_lds(split_allpairs_kernel<ALGO, S, kAllPairsNS>, SH::LDS_BYTES);
   if (once != MG_OK) return once;
   hipLaunchKernelGGL(batched_fill_kernel, dim3((unsigned)blocks[0]), dim3(256), 0, s, d_desc,
                      d_first, nl);
   hipLaunchKernelGGL(batched_exp_rows_kernel<ESZ>, dim3((unsigned)blocks[1]), dim3(256), 0, s,
-                     d_desc, d_first + (nl + 1), nl, S, bits);
+                     d_desc, d_first + (nl + 1), nl);
   hipLaunchKernelGGL(batched_slice_cols_kernel<ESZ>, dim3((unsigned)blocks[2]), dim3(256), 0, s,
-                     d_desc, d_first + 2 * (nl + 1), nl, S, bits);
+                     d_desc, d_first + 2 * (nl + 1), nl);
   hipLaunchKernelGGL((split_allpairs_kernel<ALGO, S, kAllPairsNS>), dim3((unsigned)ntiles),
                      dim3(256), SH::LDS_BYTES, s, d_args, d_recs);
   MG_HIP_TRY(hipGetLastError());
