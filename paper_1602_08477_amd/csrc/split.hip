@@ -484,45 +484,48 @@ __device__ __forceinline__ void fold_partials(typename M::acc_t (&acc)[FMW][FNW]
     }
 }
 
-// C = alpha * 2^(E_i + F_j) * fin + beta * C for one block of this lane's
-// outputs (rows rowb .. rowb+3, columns col0 + 16j), each product and the sum
-// rounded once.  Every operand (E, F, and C when beta != 0) is loaded first,
-// from addresses clamped into the matrix, so the loads are in flight
-// together (one memory round trip, not one per output); values of rows or
-// columns outside the matrix are computed and not stored.
-template <int FNW>
-__device__ __forceinline__ void store_block(const SplitArgs &a, const double (&fin)[4][FNW],
-                                            int rowb, int col0) {
-  int er[4], fc[FNW], cc[FNW];
-  int64_t roff[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = min(rowb + r, a.m - 1);
-    er[r] = a.E[row];
-    roff[r] = (int64_t)row * a.ldc;
-  }
+// C = alpha * 2^(E_i + F_j) * fin + beta * C for this lane's outputs (rows
+// row0 + 16i + 0 .. 3, columns col0 + 16j), each product and the sum rounded
+// once.  Every operand (E, F, and C when beta != 0) is loaded first, from
+// addresses clamped into the matrix, so the loads are in flight together (one
+// memory round trip, not one per output); values of rows or columns outside
+// the matrix are computed and not stored.
+template <int FM, int FNW>
+__device__ __forceinline__ void store_block(const SplitArgs &a, const double (&fin)[FM][4][FNW],
+                                            int row0, int col0) {
+  int er[FM][4], fc[FNW], cc[FNW];
+  double cv[FM][4][FNW];
+  const bool with_c = a.beta != 0.0;
 #pragma unroll
   for (int j = 0; j < FNW; ++j) {
     cc[j] = min(col0 + 16 * j, a.n - 1);
     fc[j] = a.F[cc[j]];
   }
-  const bool with_c = a.beta != 0.0;
-  double cv[4][FNW];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) er[i][r] = a.E[min(row0 + 16 * i + r, a.m - 1)];
   if (with_c) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int j = 0; j < FNW; ++j)
+          cv[i][r][j] = a.C[(int64_t)min(row0 + 16 * i + r, a.m - 1) * a.ldc + cc[j]];
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int j = 0; j < FNW; ++j) cv[r][j] = a.C[roff[r] + cc[j]];
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int j = 0; j < FNW; ++j) {
-      const double prod = ldexp(fin[r][j], er[r] + fc[j]);
-      double o = __dmul_rn(a.alpha, prod);
-      if (with_c) o = __dadd_rn(o, __dmul_rn(a.beta, cv[r][j]));
-      if (rowb + r < a.m && col0 + 16 * j < a.n) a.C[roff[r] + cc[j]] = o;
-    }
+      for (int j = 0; j < FNW; ++j) {
+        const int row = row0 + 16 * i + r;
+        const double prod = ldexp(fin[i][r][j], er[i][r] + fc[j]);
+        double o = __dmul_rn(a.alpha, prod);
+        if (with_c) o = __dadd_rn(o, __dmul_rn(a.beta, cv[i][r][j]));
+        if (row < a.m && col0 + 16 * j < a.n) a.C[(int64_t)row * a.ldc + cc[j]] = o;
+      }
 }
 
 // Last fold, then the epilogue.  (row0, col0): this lane's first output.
@@ -537,16 +540,16 @@ __device__ __forceinline__ void finish_tile(const SplitArgs &a, typename M::acc_
   for (int i = 0; i < FMW; ++i)
 #pragma unroll
     for (int j0 = 0; j0 < FNW; j0 += CJ) {
-      double fin[4][CJ];
+      double fin[1][4][CJ];
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int j = 0; j < CJ; ++j) {
           const int v = M::CHUNK_STAGES > 0 ? dacc[i][j0 + j][r] : (int)acc[i][j0 + j][r];
           const double part = only ? 0.0 : plane[((i * FNW + j0 + j) * 4 + r) * THREADS];
-          fin[r][j] = fma((double)v, sc, part);
+          fin[0][r][j] = fma((double)v, sc, part);
         }
-      store_block<CJ>(a, fin, row0 + 16 * i, col0 + 16 * j0);
+      store_block<1, CJ>(a, fin, row0 + 16 * i, col0 + 16 * j0);
       __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -1267,202 +1270,216 @@ __global__ __launch_bounds__(256) void batched_slice_cols_kernel(const SplitPrep
 // k stage of 64 bytes (64 INT8 / 32 BF16 values, one MFMA per 16x16 block)
 // all S slices of A and all S slices of B for the tile are in LDS at once
 // and every slice pair (p, q), p + q <= S + 1, is multiplied from them into
-// one exact INT32 accumulator set per diagonal d = p + q, held in registers
-// with the FP64 partial sums.  So each slice byte is read from memory once
-// per tile (the pair-major walk reads slice p of A once for each of its
-// S + 1 - p diagonals).  At the end of each k segment the diagonals fold in
-// increasing d, the fold order of the other divisions: P_d of a segment is
-// the same exact integer whatever order its pairs and stages are summed
-// in, so the result is the same bit for bit.
-// NS = 2: a 2-stage ring, one workgroup per CU; NS = 1: one stage, refilled
-// after every workgroup has read it, two workgroups per CU (each one's loads
-// and per-tile work overlap the other's products).
-template <int S, int NS_ = 2>
+// one exact INT32 accumulator set per diagonal d = p + q, held in registers.
+// So each slice byte is read from memory once per tile (the pair-major walk
+// reads slice p of A once for each of its S + 1 - p diagonals).  At the end
+// of each k segment the diagonals fold in increasing d, the fold order of the
+// other divisions: P_d of a segment is the same exact integer whatever order
+// its pairs and stages are summed in, so the result is the same bit for bit.
+//
+// One stage of LDS, two workgroups per CU.  A wavefront takes all its
+// fragments of a stage into registers, and the place is refilled under the
+// products; with the refill after the products its time was exposed.  In a
+// product of several k segments the FP64 partial sums hold those registers:
+// there the refill waits for the products.
+template <int S>
 struct AllPairsShape {
-  static constexpr int THREADS = 256, BM = 64, BN = 64, SB = 64, NS = NS_, FMW = 2, FNW = 2;
-  static constexpr int SLICE = 64 * SB;         // one slice's tile rows for one stage
-  static constexpr int STAGE = 2 * S * SLICE;   // S slices of A, then S of B
-  static constexpr size_t LDS_BYTES = (size_t)NS * STAGE;
-  static_assert(LDS_BYTES <= 160 * 1024, "stage ring beyond the CU's LDS");
+  static constexpr int THREADS = 256, BM = 64, BN = 64, SB = 64, FMW = 2, FNW = 2;
+  static constexpr int SLICE = 64 * SB;        // one slice's tile rows for one stage
+  static constexpr int STAGE = 2 * S * SLICE;  // S slices of A, then S of B
+  static constexpr size_t LDS_BYTES = STAGE;
+  static_assert(2 * LDS_BYTES <= 160 * 1024, "two workgroups per CU");
 };
 
-// Epilogue of an all-pairs tile: the last diagonal's integer sums, folded
-// onto the partial sums, then C as in finish_tile.
-template <int FMW, int FNW>
-__device__ __forceinline__ void finish_ints(const SplitArgs &a, const i4v (&last)[FMW][FNW],
-                                            const double (&part)[FMW][FNW][4], bool only,
-                                            int row0, int col0) {
-  const double sc = ldexp(1.0, -a.bits * (a.s + 1));
-#pragma unroll
-  for (int i = 0; i < FMW; ++i) {
-    double fin[4][FNW];
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-#pragma unroll
-      for (int j = 0; j < FNW; ++j)
-        fin[r][j] = fma((double)last[i][j][r], sc, only ? 0.0 : part[i][j][r]);
-    store_block<FNW>(a, fin, row0 + 16 * i, col0);
-  }
-}
+// Every LDS read of this wavefront has returned.
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // `a.seg_stages` and `a.total_stages` count 64-byte stages here; a.s == S.
-template <int ALGO, int S, int NS>
+// EARLY: refill under the products (one k segment).
+template <int ALGO, int S, bool EARLY>
 __device__ __forceinline__ void split_allpairs_tile(const SplitArgs &a, int m0, int n0,
                                                     unsigned char *lds) {
-  typedef AllPairsShape<S, NS> SH;
+  typedef AllPairsShape<S> SH;
   constexpr int FMW = SH::FMW, FNW = SH::FNW, SB = SH::SB, SL = SH::SLICE;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * 32;
   const int g = lane >> 4, l16 = lane & 15;
   const int64_t a_slice = (int64_t)a.mp * a.kp_bytes, b_slice = (int64_t)a.np * a.kp_bytes;
   // DMA: wavefront w loads rows 16w .. 16w+15 of every slice (1 KB per
   // instruction); the lane supplies row 16w + lane/4, physical chunk lane%4,
-  // which holds logical chunk swz_chunk(row, lane%4).
-  const int drow = 16 * wave + (lane >> 2);
-  const int64_t asrc = (int64_t)(m0 + drow) * a.kp_bytes + swz_chunk<SB>(drow, lane & 3) * 16;
-  const int64_t bsrc = (int64_t)(n0 + drow) * a.kp_bytes + swz_chunk<SB>(drow, lane & 3) * 16;
-  auto issue = [&](int st, int stage) {
-    const int64_t koff = (int64_t)st * SB;
-    unsigned char *la = lds + stage * SH::STAGE + wave * 1024;
+  // which holds logical chunk swz_chunk(row, lane%4).  The wavefront's first
+  // row is a scalar address: one 32-bit offset per lane serves every slice.
+  // (15 rows stay below 2^32 bytes: two operands' 256 padded rows fit memory.)
+  const unsigned loff = (unsigned)(lane >> 2) * (unsigned)a.kp_bytes +
+                        swz_chunk<SB>(16 * wave + (lane >> 2), lane & 3) * 16;
+  const unsigned char *asrc = a.As + (int64_t)(m0 + 16 * wave) * a.kp_bytes;
+  const unsigned char *bsrc = a.Bs + (int64_t)(n0 + 16 * wave) * a.kp_bytes;
+  auto issue = [&](int st) {
+    const unsigned char *pa = asrc + (int64_t)st * SB, *pb = bsrc + (int64_t)st * SB;
+    asm("" : "+s"(pa), "+s"(pb));  // addresses of a stage, not one per lane and slice
+    unsigned char *la = lds + wave * 1024;
 #pragma unroll
-    for (int t = 0; t < S; ++t) dma16(a.As + t * a_slice + asrc + koff, la + t * SL);
+    for (int t = 0; t < S; ++t) dma16(pa + t * a_slice + loff, la + t * SL);
 #pragma unroll
-    for (int t = 0; t < S; ++t) dma16(a.Bs + t * b_slice + bsrc + koff, la + (S + t) * SL);
+    for (int t = 0; t < S; ++t) dma16(pb + t * b_slice + loff, la + (S + t) * SL);
   };
 
   i4v acc[S][FMW][FNW];  // INT32 sums of the diagonals d = 2 .. S+1 (index d - 2)
-  double part[FMW][FNW][4];
-#pragma unroll
-  for (int d = 0; d < S; ++d)
-#pragma unroll
-    for (int i = 0; i < FMW; ++i)
-#pragma unroll
-      for (int j = 0; j < FNW; ++j) acc[d][i][j] = i4v{};
+  double part[FMW][4][FNW];
 #pragma unroll
   for (int i = 0; i < FMW; ++i)
 #pragma unroll
-    for (int j = 0; j < FNW; ++j)
+    for (int j = 0; j < FNW; ++j) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) part[i][j][r] = 0.0;
+      for (int d = 0; d < S; ++d) acc[d][i][j] = i4v{};
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[i][r][j] = 0.0;
+    }
 
   const int T = a.total_stages;
   bool first = true;  // no fold yet: the first starts from 0
-  if constexpr (NS == 2) {
-    MG_LDS_POISON_STAGE(lds, SH::NS * SH::STAGE);
-    issue(0, 0);
-  }
-  for (int t = 0; t < T; ++t) {
-    if constexpr (NS == 1) {
-      MG_LDS_POISON_STAGE(lds, SH::STAGE);
-      issue(t, 0);
+  // Folds every diagonal, in increasing d.
+  auto fold = [&]() {
+#pragma unroll
+    for (int d = 0; d < S; ++d) {
+      const double sc = ldexp(1.0, -a.bits * (d + 2));
+#pragma unroll
+      for (int i = 0; i < FMW; ++i)
+#pragma unroll
+        for (int j = 0; j < FNW; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            part[i][r][j] = fma((double)acc[d][i][j][r], sc, first ? 0.0 : part[i][r][j]);
+            acc[d][i][j][r] = 0;
+          }
+      first = false;
     }
+  };
+  // every wavefront has its fragments: the next stage may land
+  auto refill = [&](int st) {
+    wait_lds();
+    __builtin_amdgcn_s_barrier();
+    if (st < T) {
+      MG_LDS_POISON_STAGE(lds, SH::STAGE);
+      issue(st);
+    }
+  };
+
+  MG_LDS_POISON_STAGE(lds, SH::STAGE);
+  issue(0);
+  for (int t = 0; t < T; ++t) {
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
-    if constexpr (NS == 2) {
-      if (t + 1 < T) {
-        MG_LDS_POISON_STAGE(lds + ((t + 1) & 1) * SH::STAGE, SH::STAGE);
-        issue(t + 1, (t + 1) & 1);
-      }
-    }
-    const unsigned char *As = lds + (NS == 2 ? (t & 1) : 0) * SH::STAGE;
-    const unsigned char *Bs = As + S * SL;
-    i4v fb[S][FNW];
+    i4v fa[S][FMW], fb[S][FNW];
 #pragma unroll
-    for (int q = 0; q < S; ++q)
-#pragma unroll
-      for (int j = 0; j < FNW; ++j) {
-        const int row = wn0 + 16 * j + l16;
-        fb[q][j] = *reinterpret_cast<const i4v *>(Bs + q * SL + row * SB +
-                                                  swz_chunk<SB>(row, g) * 16);
-      }
-#pragma unroll
-    for (int p = 0; p < S; ++p) {
-      i4v fa[FMW];
+    for (int q = 0; q < S; ++q) {
 #pragma unroll
       for (int i = 0; i < FMW; ++i) {
         const int row = wm0 + 16 * i + l16;
-        fa[i] = *reinterpret_cast<const i4v *>(As + p * SL + row * SB +
-                                               swz_chunk<SB>(row, g) * 16);
+        fa[q][i] = *reinterpret_cast<const i4v *>(lds + q * SL + row * SB +
+                                                  swz_chunk<SB>(row, g) * 16);
       }
 #pragma unroll
-      for (int q = 0; q < S - p; ++q)
-#pragma unroll
-        for (int i = 0; i < FMW; ++i)
-#pragma unroll
-          for (int j = 0; j < FNW; ++j) {
-            if constexpr (ALGO == MG_SPLIT_I8) {
-              acc[p + q][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[q][j],
-                                                                       acc[p + q][i][j], 0, 0, 0);
-            } else {  // 32 products of |x| <= 255^2: exact in FP32, then added as integers
-              const f4v c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  __builtin_bit_cast(bf8v, fa[i]), __builtin_bit_cast(bf8v, fb[q][j]), f4v{},
-                  0, 0, 0);
-#pragma unroll
-              for (int r = 0; r < 4; ++r) acc[p + q][i][j][r] += (int)c[r];
-            }
-          }
+      for (int j = 0; j < FNW; ++j) {
+        const int row = wn0 + 16 * j + l16;
+        fb[q][j] = *reinterpret_cast<const i4v *>(lds + (S + q) * SL + row * SB +
+                                                  swz_chunk<SB>(row, g) * 16);
+      }
     }
-    // one stage: every wavefront has read it before the next load overwrites it
-    if constexpr (NS == 1) __builtin_amdgcn_s_barrier();
-    // End of a k segment (but not the last): fold every diagonal, increasing d.
-    if (t + 1 < T && (t + 1) % a.seg_stages == 0) {
+    if (EARLY) refill(t + 1);
+    if constexpr (ALGO == MG_SPLIT_I8) {
+#pragma unroll
+      for (int p = 0; p < S; ++p)
+#pragma unroll
+        for (int q = 0; q < S - p; ++q)
+#pragma unroll
+          for (int i = 0; i < FMW; ++i)
+#pragma unroll
+            for (int j = 0; j < FNW; ++j)
+              acc[p + q][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[p][i], fb[q][j],
+                                                                       acc[p + q][i][j], 0, 0, 0);
+    } else {
 #pragma unroll
       for (int d = 0; d < S; ++d) {
-        const double sc = ldexp(1.0, -a.bits * (d + 2));
+        // At most 6 * 32 products of |x| <= 255^2: exact in FP32.  Added as
+        // integers once per diagonal (once per pair bounded the tile before:
+        // BF16 n = 1024, 122 us).
+        f4v c[FMW][FNW];
+#pragma unroll
+        for (int p = 0; p <= d; ++p)
+#pragma unroll
+          for (int i = 0; i < FMW; ++i)
+#pragma unroll
+            for (int j = 0; j < FNW; ++j)
+              c[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf8v, fa[p][i]), __builtin_bit_cast(bf8v, fb[d - p][j]),
+                  p == 0 ? f4v{} : c[i][j], 0, 0, 0);
 #pragma unroll
         for (int i = 0; i < FMW; ++i)
 #pragma unroll
           for (int j = 0; j < FNW; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              part[i][j][r] = fma((double)acc[d][i][j][r], sc, first ? 0.0 : part[i][j][r]);
-              acc[d][i][j][r] = 0;
-            }
-        first = false;
+            for (int r = 0; r < 4; ++r) acc[d][i][j][r] += (int)c[i][j][r];
       }
     }
+    if (!EARLY) {
+      refill(t + 1);
+      if (t + 1 < T && (t + 1) % a.seg_stages == 0) fold();
+    }
   }
-  // Last segment: diagonals 2 .. S, then the last one in the epilogue.
-#pragma unroll
-  for (int d = 0; d < S - 1; ++d) {
-    const double sc = ldexp(1.0, -a.bits * (d + 2));
-#pragma unroll
-    for (int i = 0; i < FMW; ++i)
-#pragma unroll
-      for (int j = 0; j < FNW; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          part[i][j][r] = fma((double)acc[d][i][j][r], sc, first ? 0.0 : part[i][j][r]);
-    first = false;
-  }
-  finish_ints<FMW, FNW>(a, acc[S - 1], part, first, m0 + wm0 + 4 * g, n0 + wn0 + l16);
+  fold();
+  store_block<FMW, FNW>(a, part, m0 + wm0 + 4 * g, n0 + wn0 + l16);
 }
 
-template <int ALGO, int S, int NS>
-__global__ __launch_bounds__(256, NS == 1 ? 2 : 1) void split_allpairs_kernel(
-    const SplitArgs *args, const SplitTileRec *recs) {
+// When a place is refilled early.  Workgroups whose loads are hidden drift
+// apart over a large product and stop sharing slices in their XCD's L2 (INT8
+// n = 4096: 85 M L2 misses a launch against 24 M, 1.71 against 1.52 ms); with
+// the loads exposed the ones ahead wait for memory and the ones behind catch
+// up from L2.  So: up to 2048 tiles (four rounds of 512 workgroups), or while
+// the slices of the 8x8 tiles that an XCD works on, all their k, fit its L2
+// (4 MB).  Whole calls, early against late: INT8 n = 512 / 1024 / 1536 / 2500
+// 29.0 / 46.3 / 124 / 431 against 32.6 / 55.2 / 139 / 449 us, n = 3000 / 4096
+// 761 / 1858 against 725 / 1649, 4096 x 4096 x 512 217 against 239; BF16
+// n = 1024 / 2500 / 4096 65 / 688 / 3073 against 86 / 744 / 2866.
+constexpr int kEarlyTiles = 2048;
+constexpr int64_t kXcdL2 = 4 << 20;
+
+template <int ALGO, int S>
+__device__ __forceinline__ void split_allpairs_any(const SplitArgs &a, int m0, int n0,
+                                                   unsigned char *lds) {
+  const int64_t tiles = (int64_t)((a.m + 63) >> 6) * ((a.n + 63) >> 6);
+  const bool shared = tiles > kEarlyTiles && a.kp_bytes * (S * 16 * 64) > kXcdL2;
+  if (!shared && a.seg_stages >= a.total_stages)
+    split_allpairs_tile<ALGO, S, true>(a, m0, n0, lds);
+  else
+    split_allpairs_tile<ALGO, S, false>(a, m0, n0, lds);
+}
+
+template <int ALGO, int S>
+__global__ __launch_bounds__(256, 2) void split_allpairs_kernel(const SplitArgs *args,
+                                                                const SplitTileRec *recs) {
   extern __shared__ __align__(16) unsigned char lds[];
   const SplitTileRec r = recs[blockIdx.x];
   if (r.prob < 0) return;  // padding of an XCD's share of the list
-  const SplitArgs a = args[r.prob];
-  split_allpairs_tile<ALGO, S, NS>(a, r.m0, r.n0, lds);
+  SplitArgs a = args[r.prob];
+  a.As = in_global(a.As);
+  a.Bs = in_global(a.Bs);
+  a.E = in_global(a.E);
+  a.F = in_global(a.F);
+  a.C = in_global(a.C);
+  split_allpairs_any<ALGO, S>(a, r.m0, r.n0, lds);
 }
 
 // The all-pairs tile over one problem's 64x64 tiles (work division 16).
-template <int ALGO, int S, int NS>
-__global__ __launch_bounds__(256, NS == 1 ? 2 : 1) void split_allpairs_grid_kernel(
-    SplitArgs a, int tiles_m, int tiles_n) {
+template <int ALGO, int S>
+__global__ __launch_bounds__(256, 2) void split_allpairs_grid_kernel(SplitArgs a, int tiles_m,
+                                                                     int tiles_n) {
   extern __shared__ __align__(16) unsigned char lds[];
   int tm, tn;
   grouped_tile(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, 8, tm, tn);
-  split_allpairs_tile<ALGO, S, NS>(a, tm * 64, tn * 64, lds);
+  split_allpairs_any<ALGO, S>(a, tm * 64, tn * 64, lds);
 }
-
-// Stages of the batched product tile: one, with two workgroups per CU
-// (measured against the 2-stage ring at one per CU, 2000-problem batch:
-// INT8 1.92 against 2.05 ms, BF16 2.53 against 3.01 ms; uniform 1024^3
-// batches 0.70 against 0.91 ms).
-constexpr int kAllPairsNS = 1;
 
 // Slice count of a batch (the all-pairs tile is built for the default).
 constexpr int batch_slices(int algo) { return algo == MG_SPLIT_BF16 ? 6 : 7; }
@@ -1473,8 +1490,8 @@ int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const
                      hipStream_t s) {
   constexpr int ESZ = ALGO == MG_SPLIT_BF16 ? 2 : 1;
   constexpr int S = batch_slices(ALGO);
-  typedef AllPairsShape<S, kAllPairsNS> SH;
-  static int once = ensure_lds(split_allpairs_kernel<ALGO, S, kAllPairsNS>, SH::LDS_BYTES);
+  typedef AllPairsShape<S> SH;
+  static int once = ensure_lds(split_allpairs_kernel<ALGO, S>, SH::LDS_BYTES);
   if (once != MG_OK) return once;
   hipLaunchKernelGGL(batched_fill_kernel, dim3((unsigned)blocks[0]), dim3(256), 0, s, d_desc,
                      d_first, nl);
@@ -1482,7 +1499,7 @@ int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const
                      d_desc, d_first + (nl + 1), nl);
   hipLaunchKernelGGL(batched_slice_cols_kernel<ESZ>, dim3((unsigned)blocks[2]), dim3(256), 0, s,
                      d_desc, d_first + 2 * (nl + 1), nl);
-  hipLaunchKernelGGL((split_allpairs_kernel<ALGO, S, kAllPairsNS>), dim3((unsigned)ntiles),
+  hipLaunchKernelGGL((split_allpairs_kernel<ALGO, S>), dim3((unsigned)ntiles),
                      dim3(256), SH::LDS_BYTES, s, d_args, d_recs);
   MG_HIP_TRY(hipGetLastError());
   return MG_OK;
@@ -1494,12 +1511,12 @@ int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const
 template <int ALGO>
 int launch_allpairs_t(const SplitArgs &a128, hipStream_t s) {
   constexpr int S = batch_slices(ALGO);
-  typedef AllPairsShape<S, kAllPairsNS> SH;
+  typedef AllPairsShape<S> SH;
   if (a128.s != S) {
     set_error("split work division 16 takes the default slice count (%d)", S);
     return MG_ERR_INVALID_ARG;
   }
-  auto kern = split_allpairs_grid_kernel<ALGO, S, kAllPairsNS>;
+  auto kern = split_allpairs_grid_kernel<ALGO, S>;
   static int once = ensure_lds(kern, SH::LDS_BYTES);
   if (once != MG_OK) return once;
   SplitArgs a = a128;  // stage counts in 64-byte stages
@@ -1665,17 +1682,17 @@ int split_num_cfgs() { return 17; }
 // register-staged 128x128 tile.
 int split_pick_cfg(int algo, int slices, int64_t mp, int64_t np, bool latency) {
   // For one call's latency, at the default slice count, the all-pairs 64x64
-  // tile (16): INT8 at every size, BF16 up to n = 1024.  Whole INT8 call n =
-  // 256 / 512 / 1024: 50 / 57 / 90 us against 76 / 100 / 139 for the
+  // tile (16): each slice byte is read once per tile.  Whole INT8 call n =
+  // 256 / 512 / 1024: 20 / 29 / 46 us against 76 / 100 / 139 for the
   // pair-parallel division and the 128x128 ring; products with a held
   // workspace, n = 2048 / 3072 / 4096 / 5120 / 6144 / 8192: 0.21 / 0.73 /
   // 1.61 / 3.17 / 5.52 / 11.99 ms against 0.23 / 1.57 / 1.78 / 4.20 / 7.33 /
   // 12.69 for the 256x256 ring (whose tiles fill the chip only at n = 4096
-  // and 8192).  BF16 n = 1024: 163 against 223 us; n = 2048 / 3072 about
-  // even, n = 4096 4.24 against 3.19 ms (its FP32-to-INT32 conversions).
-  if (latency && slices == split_default_slices(algo) &&
-      (algo == MG_SPLIT_I8 || mp * np <= (int64_t)1024 * 1024))
-    return 16;
+  // and 8192).  Whole BF16 call n = 1024 / 2048 / 4096 / 8192: 65 us / 0.34 /
+  // 2.85 / 23.9 ms against 201 us (15) / 0.53 (12) / 3.34 (2) / 27.4 (2);
+  // 2048 x 2048 x 256 63 against 115 us (12), 128 x 4096 x 1024 71 against
+  // 181 (15).
+  if (latency && slices == split_default_slices(algo)) return 16;
   // Other slice counts below one 128x128 tile per CU: the pair-parallel
   // division (15): the fused divisions would give too few workgroups, each
   // walking all the slice pairs as one chain of dependent loads.  When the
