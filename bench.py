@@ -553,7 +553,7 @@ def batched_oracle_error(shapes, offs, flats, C_init):
 
 def bench_batched(steps):
     """2000 problems, m, n, k log-uniform in [16, 512], FP64 and FP32: one
-    persistent launch per batch, graph-replayed, tile classes autotuned."""
+    launch per batch, graph-replayed, tile classes autotuned."""
     import torch
     import paper_1602_08477_amd as mg
     import synth
