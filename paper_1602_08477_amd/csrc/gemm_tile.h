@@ -355,6 +355,12 @@ struct Epilogue<float> {
               const int row = row0 + 16 * (i0 + i) + Mfma<float>::row_of(gq, r);
               c[i][jb][r] = g.C[(int64_t)min(row, g.m - 1) * g.ldc + min(col0 + 16 * jb + j, g.n - 1)];
             }
+        // One wait for all loads, here: the compiler's own, in the branch of
+        // each store, also waits for the stores before it (one counter): 2000
+        // problems in one launch 242 -> 238 us.  FP64 tiles, whose 16-byte
+        // stores are fewer, lose by it (n = 2048 249 -> 254 us).
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0, the others at their maxima
       }
 #pragma unroll
       for (int i = 0; i < R; ++i)
