@@ -11,7 +11,7 @@
 // What bounds it: memory, for a batch of small problems.  2000 problems of
 // extents 16-512 (1.32 GB, 11.1 GFLOP, 17.9 on 64x64 tiles): 411 us in FP64 =
 // 3.2 TB/s (on 64x64 tiles alone 419 when measured: 345 without the products,
-// 325 without the C traffic, 210 with neither); FP32 241 us.  A persistent
+// 325 without the C traffic, 210 with neither); FP32 236 us.  A persistent
 // kernel that streamed a workgroup's tiles through one LDS ring of 4-byte
 // loads (any alignment) took 650 and 401 us: four times the load instructions,
 // one register allocation for every path, and a static deal of the tiles.
