@@ -1300,9 +1300,15 @@ struct AllPairsShape {
 // Every LDS read of this wavefront has returned.
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// A lane's DMA offset within its wavefront's 16 slice rows: row r (0 .. 15),
+// byte c of the 64-byte stage.  32 bits while row 15 fits: a 64-bit offset per
+// lane takes registers and vector adds from the product loop.
+constexpr int64_t kMaxKpBytes32 = ((int64_t)UINT32_MAX - 63) / 15;
+
 // `a.seg_stages` and `a.total_stages` count 64-byte stages here; a.s == S.
-// EARLY: refill under the products (one k segment).
-template <int ALGO, int S, bool EARLY>
+// EARLY: refill under the products (one k segment).  Off: the type of a lane's
+// offset (32 bits up to kMaxKpBytes32).
+template <int ALGO, int S, bool EARLY, typename Off>
 __device__ __forceinline__ void split_allpairs_tile(const SplitArgs &a, int m0, int n0,
                                                     unsigned char *lds) {
   typedef AllPairsShape<S> SH;
@@ -1315,10 +1321,9 @@ __device__ __forceinline__ void split_allpairs_tile(const SplitArgs &a, int m0, 
   // DMA: wavefront w loads rows 16w .. 16w+15 of every slice (1 KB per
   // instruction); the lane supplies row 16w + lane/4, physical chunk lane%4,
   // which holds logical chunk swz_chunk(row, lane%4).  The wavefront's first
-  // row is a scalar address: one 32-bit offset per lane serves every slice.
-  // (15 rows stay below 2^32 bytes: two operands' 256 padded rows fit memory.)
-  const unsigned loff = (unsigned)(lane >> 2) * (unsigned)a.kp_bytes +
-                        swz_chunk<SB>(16 * wave + (lane >> 2), lane & 3) * 16;
+  // row is a scalar address: one offset per lane serves every slice.
+  const Off loff = (Off)(lane >> 2) * (Off)a.kp_bytes +
+                   swz_chunk<SB>(16 * wave + (lane >> 2), lane & 3) * 16;
   const unsigned char *asrc = a.As + (int64_t)(m0 + 16 * wave) * a.kp_bytes;
   const unsigned char *bsrc = a.Bs + (int64_t)(n0 + 16 * wave) * a.kp_bytes;
   auto issue = [&](int st) {
@@ -1451,18 +1456,18 @@ __device__ __forceinline__ void split_allpairs_tile(const SplitArgs &a, int m0, 
 constexpr int kEarlyTiles = 2048;
 constexpr int64_t kXcdL2 = 4 << 20;
 
-template <int ALGO, int S>
+template <int ALGO, int S, typename Off>
 __device__ __forceinline__ void split_allpairs_any(const SplitArgs &a, int m0, int n0,
                                                    unsigned char *lds) {
   const int64_t tiles = (int64_t)((a.m + 63) >> 6) * ((a.n + 63) >> 6);
   const bool shared = tiles > kEarlyTiles && a.kp_bytes * (S * 16 * 64) > kXcdL2;
   if (!shared && a.seg_stages >= a.total_stages)
-    split_allpairs_tile<ALGO, S, true>(a, m0, n0, lds);
+    split_allpairs_tile<ALGO, S, true, Off>(a, m0, n0, lds);
   else
-    split_allpairs_tile<ALGO, S, false>(a, m0, n0, lds);
+    split_allpairs_tile<ALGO, S, false, Off>(a, m0, n0, lds);
 }
 
-template <int ALGO, int S>
+template <int ALGO, int S, typename Off>
 __global__ __launch_bounds__(256, 2) void split_allpairs_kernel(const SplitArgs *args,
                                                                 const SplitTileRec *recs) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -1474,17 +1479,19 @@ __global__ __launch_bounds__(256, 2) void split_allpairs_kernel(const SplitArgs 
   a.E = in_global(a.E);
   a.F = in_global(a.F);
   a.C = in_global(a.C);
-  split_allpairs_any<ALGO, S>(a, r.m0, r.n0, lds);
+  split_allpairs_any<ALGO, S, Off>(a, r.m0, r.n0, lds);
 }
 
-// The all-pairs tile over one problem's 64x64 tiles (work division 16).
+// The all-pairs tile over one problem's 64x64 tiles (work division 16).  Both
+// operands are padded to 256 rows or more: at kMaxKpBytes32 their slices would
+// take 880 GB, so 32-bit lane offsets always do.
 template <int ALGO, int S>
 __global__ __launch_bounds__(256, 2) void split_allpairs_grid_kernel(SplitArgs a, int tiles_m,
                                                                      int tiles_n) {
   extern __shared__ __align__(16) unsigned char lds[];
   int tm, tn;
   grouped_tile(xcd_remap(blockIdx.x, tiles_m * tiles_n), tiles_m, tiles_n, 8, tm, tn);
-  split_allpairs_any<ALGO, S>(a, tm * 64, tn * 64, lds);
+  split_allpairs_any<ALGO, S, unsigned>(a, tm * 64, tn * 64, lds);
 }
 
 // Slice count of a batch (the all-pairs tile is built for the default).
@@ -1493,19 +1500,26 @@ constexpr int batch_slices(int algo) { return algo == MG_SPLIT_BF16 ? 6 : 7; }
 template <int ALGO>
 int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const int *d_first,
                      int nl, const int64_t *blocks, const SplitTileRec *d_recs, int ntiles,
-                     hipStream_t s) {
+                     int64_t max_kp_bytes, hipStream_t s) {
   constexpr int ESZ = ALGO == MG_SPLIT_BF16 ? 2 : 1;
   constexpr int S = batch_slices(ALGO);
   typedef AllPairsShape<S> SH;
-  static int once = ensure_lds(split_allpairs_kernel<ALGO, S>, SH::LDS_BYTES);
+  // A problem of up to 64 x 64 outputs keeps 128 rows of each slice, so its k
+  // can pass what a 32-bit lane offset holds within the card's memory (BF16
+  // k = 143.2 M: 220 GB of slices).
+  auto kern = split_allpairs_kernel<ALGO, S, unsigned>;
+  auto wide = split_allpairs_kernel<ALGO, S, int64_t>;
+  static int once = ensure_lds(kern, SH::LDS_BYTES);
+  static int once_wide = ensure_lds(wide, SH::LDS_BYTES);
   if (once != MG_OK) return once;
+  if (once_wide != MG_OK) return once_wide;
   hipLaunchKernelGGL(batched_fill_kernel, dim3((unsigned)blocks[0]), dim3(256), 0, s, d_desc,
                      d_first, nl);
   hipLaunchKernelGGL(batched_exp_rows_kernel<ESZ>, dim3((unsigned)blocks[1]), dim3(256), 0, s,
                      d_desc, d_first + (nl + 1), nl);
   hipLaunchKernelGGL(batched_slice_cols_kernel<ESZ>, dim3((unsigned)blocks[2]), dim3(256), 0, s,
                      d_desc, d_first + 2 * (nl + 1), nl);
-  hipLaunchKernelGGL((split_allpairs_kernel<ALGO, S>), dim3((unsigned)ntiles),
+  hipLaunchKernelGGL((max_kp_bytes > kMaxKpBytes32 ? wide : kern), dim3((unsigned)ntiles),
                      dim3(256), SH::LDS_BYTES, s, d_args, d_recs);
   MG_HIP_TRY(hipGetLastError());
   return MG_OK;
@@ -2186,11 +2200,12 @@ int gemm_split_batched(int algo, int64_t count, const mg_problem *probs, hipStre
     const auto *d_desc = reinterpret_cast<const SplitPrepDesc *>(dm + o_desc);
     const auto *d_first = reinterpret_cast<const int *>(dm + o_first);
     const auto *d_recs = reinterpret_cast<const SplitTileRec *>(dm + o_recs);
+    const int64_t max_kp_bytes = args[(size_t)ord[0]].kp_bytes;  // longest k first
     rc = algo == MG_SPLIT_BF16
              ? launch_batched_t<MG_SPLIT_BF16>(d_args, d_desc, d_first, nl, blocks, d_recs,
-                                               (int)recs.size(), s)
+                                               (int)recs.size(), max_kp_bytes, s)
              : launch_batched_t<MG_SPLIT_I8>(d_args, d_desc, d_first, nl, blocks, d_recs,
-                                             (int)recs.size(), s);
+                                             (int)recs.size(), max_kp_bytes, s);
   }
   if (buf != nullptr) return rc;
   hipEvent_t ev = nullptr;

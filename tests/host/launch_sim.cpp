@@ -1,0 +1,147 @@
+// Host side of libmg's launches, run without a GPU: this program defines the
+// HIP runtime calls that the library makes (an executable's definitions come
+// before a shared library's), so that every launch is recorded instead of
+// enqueued, memory is an address that nobody reads, and the conditions a call
+// has to cope with (a stream that is being captured, a pool that is exhausted,
+// a stream of another device) are set from here.  Checked are the kernels a
+// call picks, their grids, and their arguments.
+#include <cxxabi.h>
+#include <dlfcn.h>
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "mg.h"
+
+static int failures = 0;
+
+#define EXPECT(cond)                                                              \
+  do {                                                                            \
+    if (!(cond)) {                                                                \
+      std::fprintf(stderr, "line %d: expected %s (last error: %s)\n", __LINE__,   \
+                   #cond, mg_last_error());                                       \
+      ++failures;                                                                 \
+    }                                                                             \
+  } while (0)
+
+// ------------------------------------------------------- the device's state
+struct Launch {
+  std::string kernel;
+  dim3 grid, block;
+  std::vector<std::vector<unsigned char>> args;  // the first 16 bytes of each
+};
+static std::vector<Launch> launches;
+static std::map<const void *, std::string> &kernels() {
+  static std::map<const void *, std::string> m;  // filled by static constructors
+  return m;
+}
+static struct {
+  dim3 grid, block;
+  size_t lds;
+  hipStream_t s;
+} config;
+
+static std::string demangled(const char *name) {
+  int st = 0;
+  char *d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
+  std::string r = st == 0 ? d : name;
+  std::free(d);
+  return r;
+}
+
+static void *fake(uint64_t i) { return reinterpret_cast<void *>((i + 1) << 40); }
+
+extern "C" {
+void __hipRegisterFunction(void **modules, const void *host, char *dev, const char *name,
+                           unsigned limit, void *a, void *b, void *c, void *d, int *e) {
+  kernels()[host] = demangled(name);
+  typedef void (*F)(void **, const void *, char *, const char *, unsigned, void *, void *, void *,
+                    void *, int *);
+  static const F real = reinterpret_cast<F>(dlsym(RTLD_NEXT, "__hipRegisterFunction"));
+  real(modules, host, dev, name, limit, a, b, c, d, e);
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, hipStream_t s) {
+  config = {grid, block, lds, s};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipStream_t *s) {
+  *grid = config.grid;
+  *block = config.block;
+  *lds = config.lds;
+  *s = config.s;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **, size_t, hipStream_t) {
+  launches.push_back({kernels()[f], grid, block, {}});
+  return hipSuccess;
+}
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetDevice(int *d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
+  *v = 256;
+  return hipSuccess;
+}
+hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
+  *p = static_cast<hipMemPool_t>(fake(90));
+  return hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMallocFromPoolAsync(void **p, size_t, hipMemPool_t, hipStream_t) {
+  *p = fake(91);
+  return hipSuccess;
+}
+hipError_t hipFreeAsync(void *, hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+  *e = static_cast<hipEvent_t>(fake(92));
+  return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+}
+
+// ------------------------------------------------------------------- checks
+static mg_problem problem(int64_t m, int64_t n, int64_t k, int c) {
+  return mg_problem{m, n, k, 1.0, 1.0, fake(1), k, fake(2), n, fake(c), n};
+}
+
+// The batched split product's lane offsets: row 15 of a slice, 15 * kp_bytes
+// plus a byte of the 64-byte stage, has to fit the offset's type.
+static void split_batch_offsets() {
+  struct {
+    int algo;
+    int64_t k;
+    bool wide;
+  } cases[] = {{MG_SPLIT_I8, 4096, false},          {MG_SPLIT_BF16, 4096, false},
+               {MG_SPLIT_BF16, 143165568, false},   {MG_SPLIT_BF16, 143165569, true},
+               {MG_SPLIT_BF16, 143200000, true},    {MG_SPLIT_I8, 286331136, false},
+               {MG_SPLIT_I8, 286331137, true},      {MG_SPLIT_BF16, 170000000, true}};
+  for (const auto &c : cases) {
+    const int64_t kp_bytes = (c.k + 63) / 64 * 64 * (c.algo == MG_SPLIT_BF16 ? 2 : 1);
+    EXPECT((15 * kp_bytes + 63 > (int64_t)UINT32_MAX) == c.wide);
+    launches.clear();
+    const mg_problem p[2] = {problem(16, 24, 200, 3), problem(16, 64, c.k, 4)};
+    EXPECT(mg_gemm_batched(MG_F64, c.algo, 2, p, nullptr) == MG_OK);
+    const std::string &prod = launches.empty() ? "" : launches.back().kernel;
+    EXPECT(prod.find("split_allpairs_kernel<") != std::string::npos);
+    EXPECT((prod.find(", long>") != std::string::npos) == c.wide);
+  }
+}
+
+int main() {
+  split_batch_offsets();
+  std::printf("host launches: %d failures\n", failures);
+  return failures != 0;
+}
