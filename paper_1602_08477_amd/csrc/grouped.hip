@@ -292,11 +292,18 @@ int occupancy_t(int *cus, int *occ) {
   return MG_OK;
 }
 
+// A dispatch counts work-items in 32 bits: longer lists (17 M problems of one
+// tile) go in whole rounds over several launches.
 template <typename T>
 int launch_t(const void *d_tiles, int ntiles, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(grouped_kernel<T>, dim3(ntiles), dim3(kTileThreads), grouped_lds_bytes<T>(), s,
-                     static_cast<const GTileRec<T> *>(d_tiles), ntiles, grid);
-  MG_HIP_TRY(hipGetLastError());
+  const int most = (int)(UINT32_MAX / kTileThreads) / grid * grid;
+  const GTileRec<T> *tiles = static_cast<const GTileRec<T> *>(d_tiles);
+  for (int64_t first = 0; first < ntiles; first += most) {
+    const int part = (int)std::min<int64_t>(most, ntiles - first);
+    hipLaunchKernelGGL(grouped_kernel<T>, dim3(part), dim3(kTileThreads), grouped_lds_bytes<T>(), s,
+                       tiles + first, part, grid);
+    MG_HIP_TRY(hipGetLastError());
+  }
   return MG_OK;
 }
 

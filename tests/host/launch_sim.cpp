@@ -90,6 +90,16 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
   *v = 256;
   return hipSuccess;
 }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {
+  *n = 3;
+  return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t) {
+  *p = fake(93);
+  return hipSuccess;
+}
+hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipMemcpy(void *, const void *, size_t, hipMemcpyKind) { return hipSuccess; }
 hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
   *p = static_cast<hipMemPool_t>(fake(90));
   return hipSuccess;
@@ -140,8 +150,30 @@ static void split_batch_offsets() {
   }
 }
 
+// A batch's list of 64x64 tiles (C <- beta C, two rows of tiles): every tile
+// runs, and no dispatch has more work-items than its 32-bit count holds.
+static void batch_dispatches() {
+  for (int64_t tiles : {2ll, 1000ll, (1ll << 24) - 2, 1ll << 24, (1ll << 24) + 6}) {
+    const int64_t n = tiles / 2 * 64;
+    const mg_problem p{65, n, 0, 0.0, 0.5, nullptr, 1, nullptr, n, fake(3), n};
+    launches.clear();
+    mg_plan *plan = nullptr;
+    EXPECT(mg_plan_create(MG_F32, 1, &p, nullptr, &plan) == MG_OK);
+    EXPECT(mg_plan_launch_direct(plan, nullptr) == MG_OK);
+    int64_t run = 0;
+    for (const Launch &l : launches) {
+      EXPECT(l.kernel.find("grouped_kernel<") != std::string::npos);
+      EXPECT((uint64_t)l.grid.x * l.block.x <= UINT32_MAX && l.grid.y == 1 && l.grid.z == 1);
+      run += l.grid.x;
+    }
+    EXPECT(run == tiles);
+    EXPECT(mg_plan_destroy(plan) == MG_OK);
+  }
+}
+
 int main() {
   split_batch_offsets();
+  batch_dispatches();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
