@@ -141,6 +141,15 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
   // 122.8 on 16.
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int KU32 = F64 ? 1 : 2;
+  // 128x128 tiles on 16 wavefronts (13, the FP64 ring 21 and what 17, 21 and 22
+  // fall back to) run on 8 where 16 would be more work-items than a dispatch
+  // holds: the same sums.
+  const bool many = ((int64_t)g.m + 127) / 128 * (((int64_t)g.n + 127) / 128) * 1024 >
+                    (int64_t)UINT32_MAX;
+  auto reg128 = [&] {
+    return many ? launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, ks, s)
+                : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+  };
   switch (cfg) {
     case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, ks, s);
     case 1: return launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
@@ -155,7 +164,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
     case 10: return launch_one<T, 256, 128, 4, 2, 1, TA, TB>(g, ks, s);
     case 11: return launch_one<T, 128, 256, 2, 4, 1, TA, TB>(g, ks, s);
     case 12: return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
-    case 13: return launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+    case 13: return reg128();
     case 14:
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
@@ -166,8 +175,7 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 128, 64, 2, 2, 4, TA, TB>(g, ks, s)
                     : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 17:
-      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s)
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s) : reg128();
     case 18:
       return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
                     : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
@@ -178,12 +186,12 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 21:
-      return dma_ok ? (F64 ? launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, ks, s)
-                           : launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, ks, s))
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+      if (!dma_ok) return reg128();
+      if (!F64) return launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, ks, s);
+      return many ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s)
+                  : launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, ks, s);
     case 22:
-      return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, ks, s)
-                    : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+      return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, ks, s) : reg128();
     case 23:
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 1, KU32>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);

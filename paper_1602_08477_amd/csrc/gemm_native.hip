@@ -135,16 +135,27 @@ int64_t tiles_of(int cfg, int64_t m, int64_t n) {
   return ceil_div(m, kCfgs[cfg].bm) * ceil_div(n, kCfgs[cfg].bn);
 }
 
+// A dispatch counts work-items in 32 bits: one row of 2^29 outputs is too many
+// workgroups in 32x32 tiles, not in 128x128 ones.
+bool fits_dispatch(int cfg, int64_t m, int64_t n) {
+  const CfgDesc &c = kCfgs[cfg];
+  return tiles_of(cfg, m, n) * 64 * c.wgm * c.wgn * c.ks <= (int64_t)UINT32_MAX;
+}
+
 // 32x32 ring tiles only where an extent is below 1024: with both above, the
 // wide and tall panels they re-read twice as often as 64x32 tiles are large.
+// (If no division fits a dispatch, the launch of the one picked says so.)
 template <size_t N>
 const TileRate *best_division(const TileRate (&rates)[N], int64_t m, int64_t n) {
   const TileRate *best = nullptr;
   double cost = 0;
+  bool fits = false;
   for (const TileRate &t : rates) {
     if (t.cfg == 19 && std::min(m, n) >= 1024) continue;
+    const bool f = fits_dispatch(t.cfg, m, n);
     const double c = division_cost(t, tiles_of(t.cfg, m, n));
-    if (best == nullptr || c < cost) {
+    if (best == nullptr || (f == fits ? c < cost : f)) {
+      fits = f;
       best = &t;
       cost = c;
     }

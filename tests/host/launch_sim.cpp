@@ -171,9 +171,33 @@ static void batch_dispatches() {
   }
 }
 
+// Outputs of nearly 2^30 columns: the division picked, and the 128x128 ones
+// asked for, fit a dispatch wherever 128x128 tiles on 8 wavefronts do, and the
+// work-item count says so where they don't.
+static void long_rows() {
+  const int64_t big = 1ll << 30;
+  for (int dtype : {MG_F64, MG_F32})
+    for (int64_t off : {0, 8})  // 16-byte aligned operands, and not
+      for (int64_t m : {1, 32, 33, 64, 65, 96, 97, 128, 129, 200})
+        for (int64_t n : {(int64_t)1000, big / 8, big / 4 + 5, big / 2 - 40, big / 2, big - 128, big - 1})
+          for (int cfg : {-1, 13, 17, 21, 22}) {
+            char *A = static_cast<char *>(fake(1)) + off, *B = static_cast<char *>(fake(2)) + off;
+            launches.clear();
+            const int rc = mg_gemm_ex(dtype, cfg, 0, 0, m, n, 16, 1.0, A, 16, B, n, 0.5, fake(3), n,
+                                      nullptr);
+            const int64_t t128 = (m + 127) / 128 * ((n + 127) / 128);
+            if (t128 * 512 <= (int64_t)UINT32_MAX) EXPECT(rc == MG_OK);
+            EXPECT(rc == MG_OK || std::strstr(mg_last_error(), "too many tiles") != nullptr);
+            EXPECT(launches.size() == (rc == MG_OK ? 1u : 0u));
+            for (const Launch &l : launches)
+              EXPECT((uint64_t)l.grid.x * l.block.x <= UINT32_MAX);
+          }
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
+  long_rows();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
