@@ -73,6 +73,9 @@ struct DmaShape {
   static constexpr int FM = WM / 16, FN = WN / 16;
   // Fragments read one half step ahead (see the main loop).
   static constexpr bool AHEAD = FM * FN <= 4 && (ESZ == 8 || KS == 1);
+  // Stages in a pass of that loop, and the k from which it can run once.
+  static constexpr int UNROLL = NS * KU * (2 / KS) % 2 ? 2 * NS : NS;
+  static constexpr int LOOP_K = (UNROLL + NS) * KU * BK;
   static_assert(IA >= 1 && IA * 8 * WAVES == BM, "whole A instructions per wave");
   static_assert(IB >= 1 && IB * 8 * WAVES == BN, "whole B instructions per wave");
   static_assert(FM >= 1 && FN >= 1 && WM % 16 == 0 && WN % 16 == 0, "16x16 blocks per wave");
@@ -130,8 +133,13 @@ __device__ __forceinline__ void dma_wait_steps(int q) {
   else dma_wait_vmcnt<3 * DPS>();
 }
 
+// SHORT: the plain loop alone, for k of fewer stages than one pass of the loop
+// unrolled over the ring takes.  There the unrolled loop's set-up and its
+// remainder, which moves a second fragment set and has branches, cost a 32x32
+// tile more than reading ahead gives: FP64 200 x 2048, k = 32 / 64: 4.27 / 5.05
+// against 3.90 / 4.78 us, FP32 768 x 768 x 128 5.74 against 5.41.
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA = false, bool TB = false,
-          int KS = 1, int KU = 1>
+          int KS = 1, int KU = 1, bool SHORT = false>
 __device__ __forceinline__ void gemm_dma_tile(const GemmArgs<T> &g, int m0, int n0,
                                               unsigned char *lds) {
   typedef DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU> S;
@@ -372,7 +380,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs<T> &g, int m0, int 
   MG_LDS_POISON_STAGE(lds, NS * S::STAGE);
   int st = 0;
   Frag f[2];
-  if constexpr (S::AHEAD) {
+  if constexpr (S::AHEAD && !SHORT) {
     // Small wave tiles: the fragments of a half step are read from LDS while
     // the matrix cores work on the previous half step's.  Before the last
     // half step of stage st the wavefronts meet: stage st+1 has landed (only
@@ -389,6 +397,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs<T> &g, int m0, int 
     // Whole stages with whole refills, unrolled over the ring: LDS addresses
     // are constants and nothing branches.
     constexpr int UNR = NS * U % 2 ? 2 * NS : NS;  // fragment registers alternate
+    static_assert(UNR == S::UNROLL, "k that SHORT serves");
     for (; st + UNR + NS - 1 < SW; st += UNR) {
 #pragma unroll
       for (int j = 0; j < UNR; ++j)
@@ -446,7 +455,7 @@ __device__ __forceinline__ void gemm_dma_tile(const GemmArgs<T> &g, int m0, int 
 #pragma unroll
     for (int q = 0; q < NS - 1; ++q)
       if (q < ST) issue_stage(q);
-    for (; st + 2 * NS - 2 < SW; st += NS) {
+    for (; !SHORT && st + 2 * NS - 2 < SW; st += NS) {
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
         const int rs = (j + NS - 1) % NS;  // the ring stage refilled

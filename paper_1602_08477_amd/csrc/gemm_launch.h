@@ -31,7 +31,7 @@ __global__ __launch_bounds__((TileShape<T, BM, BN, WGM, WGN, BKM>::THREADS),
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1,
-          int KU = 1>
+          int KU = 1, bool SHORT = false>
 __global__ __launch_bounds__((DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::THREADS),
                              (DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::MINW)) void gemm_dma_kernel(
     GemmArgs<T> g, int tiles_m, int tiles_n, KSplit<T> ks) {
@@ -40,7 +40,7 @@ __global__ __launch_bounds__((DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU>::THREADS
   const int tiles = tiles_m * tiles_n;
   const int t = take_part<T, TA, TB>(g, ks, xcd_remap(blockIdx.x, tiles * ks.parts), tiles);
   grouped_tile(t, tiles_m, tiles_n, kGroupM, tm, tn);
-  gemm_dma_tile<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU>(g, tm * BM, tn * BN, lds);
+  gemm_dma_tile<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU, SHORT>(g, tm * BM, tn * BN, lds);
 }
 
 // The textbook mapping without the paper's hierarchy below the thread: one
@@ -106,7 +106,7 @@ int launch_one(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
 }
 
 template <typename T, int BM, int BN, int WGM, int WGN, int NS, bool TA, bool TB, int KS = 1,
-          int KU = 1>
+          int KU = 1, bool SHORT = false>
 int launch_dma(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
   typedef DmaShape<T, BM, BN, WGM, WGN, NS, KS, KU> S;
   const int tiles_m = (g.m + BM - 1) / BM, tiles_n = (g.n + BN - 1) / BN;
@@ -115,7 +115,7 @@ int launch_dma(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
     set_error("too many tiles (%lld) for one dispatch", (long long)tiles);
     return MG_ERR_INVALID_ARG;
   }
-  auto kern = gemm_dma_kernel<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU>;
+  auto kern = gemm_dma_kernel<T, BM, BN, WGM, WGN, NS, TA, TB, KS, KU, SHORT>;
   static const hipError_t attr = set_max_lds(kern, S::LDS_BYTES);  // once per instance
   MG_HIP_TRY(attr);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(S::THREADS), S::LDS_BYTES, s, g, tiles_m,
@@ -180,8 +180,10 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
                     : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
     case 19:
-      return dma_ok ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, ks, s)
-                    : launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
+      if (!dma_ok) return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
+      return g.k < DmaShape<T, 32, 32, 2, 2, 4>::LOOP_K
+                 ? launch_dma<T, 32, 32, 2, 2, 4, TA, TB, 1, 1, true>(g, ks, s)
+                 : launch_dma<T, 32, 32, 2, 2, 4, TA, TB>(g, ks, s);
     case 20:
       return dma_ok ? launch_dma<T, 64, 64, 4, 2, 4, TA, TB>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);

@@ -194,10 +194,26 @@ static void long_rows() {
           }
 }
 
+// The 32x32 ring's instance without the unrolled loop, below the k of one pass.
+static void short_ring() {
+  for (int dtype : {MG_F64, MG_F32})
+    for (int t = 0; t < 4; ++t)
+      for (int64_t k : {1, 16, 127, 128, 255, 256, 1000}) {
+        launches.clear();
+        EXPECT(mg_gemm_ex(dtype, 19, t & 1, t >> 1, 64, 64, k, 1.0, fake(1), 1024, fake(2), 1024,
+                          1.0, fake(3), 64, nullptr) == MG_OK);
+        EXPECT(launches.size() == 1 && launches[0].kernel.find(" 32, 32, 2, 2, 4,") !=
+                                           std::string::npos);
+        const bool plain = launches[0].kernel.find(", true>(") != std::string::npos;
+        EXPECT(plain == (k < (dtype == MG_F64 ? 128 : 256)));
+      }
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
   long_rows();
+  short_ring();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
