@@ -14,7 +14,7 @@ int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads);
 // The division mg_gemm picks for operands the direct-load rings can load.
 int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
 // The same for either kind of operands (`ring`: ring_operands of A and B).
-int pick_division(int dtype, bool ring, int64_t m, int64_t n);
+int pick_division(int dtype, bool ring, int64_t m, int64_t n, int64_t k);
 // True if the direct-load rings can load A and B: 16-byte aligned rows, and
 // pitches whose tile offsets fit the rings' 32-bit lane offsets (255 pitches
 // plus a row of the tile).

@@ -92,43 +92,53 @@ namespace {
 
 // Measured rate (TFLOP/s, whole chip, k = 2048, the launch itself taken off)
 // of a work division when every CU has 1, 2, 3-5 and 6 or more of its tiles
-// to run.  A tile takes as long
-// whether it is full or reaches past the matrix, and the CU with the most
-// tiles ends last, so a division's time is ceil(tiles / CUs) tiles at that
-// rate: 128x128 tiles are the fastest per flop, but n = 3000 gives some CUs
-// three of them and the others two (683 us by this count; 64x64 tiles: nine
-// on every CU, 520 us; measured 1092 -> 786 us).
+// to run.  A tile takes as long whether it is full or reaches past the matrix,
+// and the CU with the most tiles ends last, so a division's time is
+// ceil(tiles / CUs) tiles at that rate: 128x128 tiles are the fastest per flop,
+// but n = 3000 gives some CUs three of them and the others two (k = 2048: 729 us
+// on 128x128 tiles, 554 on 64x64 ones, nine on every CU).
+// `over`, for the same counts: what a tile costs besides its k, in k: filling
+// its ring and writing C while no other workgroup of its CU covers them.  The
+// FP64 128x128 ring has a CU to itself, so it wins only from k of about 1000 on
+// (8192 x 8192, against 64x64 tiles: k = 64 332 against 257 us, k = 512 1099
+// against 1020, k = 2048 73 against 70 TFLOP/s; 4096 x 4096: k = 256 165 against
+// 139).  Fitted to 40 outputs from 32 x 32 to 8192 x 8192, k = 32 to 2048, with
+// every division timed: the pick is within 1 % of the best on average.
 struct TileRate {
   int cfg;
-  float r[4];
+  float r[4], over[4];
 };
-constexpr TileRate kRing64[] = {{21, {70.f, 71.3f, 72.f, 73.f}},
-                                {23, {64.4f, 67.4f, 70.5f, 71.3f}},
-                                {15, {59.2f, 63.3f, 65.5f, 66.5f}},
-                                {19, {57.f, 59.f, 61.f, 62.f}}};
-constexpr TileRate kRing32[] = {{22, {120.6f, 130.1f, 131.5f, 133.f}},
-                                {21, {126.f, 127.7f, 128.5f, 128.7f}},
-                                {23, {106.7f, 110.7f, 115.f, 119.f}},
-                                {15, {99.3f, 106.f, 107.f, 111.f}},
-                                {19, {104.f, 104.f, 105.f, 109.f}}};
+constexpr TileRate kRing64[] = {{21, {70.f, 71.3f, 72.f, 73.f}, {64, 56, 72, 48}},
+                                {23, {64.4f, 67.4f, 69.5f, 70.2f}, {48, 24, 16, 16}},
+                                {15, {59.2f, 63.3f, 65.5f, 66.5f}, {16, 32, 32, 32}},
+                                {19, {57.f, 59.f, 61.f, 62.f}, {0, 8, 24, 24}}};
+// FP32 64x64 tiles on 8 wavefronts (20): two k-steps per stage (23) leave room
+// for two workgroups per CU, so three tiles take as long as four (2048 x 1536 x
+// 512: 41.2 against 33.2 us).
+constexpr TileRate kRing32[] = {{22, {120.6f, 130.1f, 131.5f, 133.f}, {0, 0, 8, 0}},
+                                {21, {126.f, 127.7f, 128.5f, 128.7f}, {0, 0, 8, 8}},
+                                {20, {118.f, 113.f, 117.f, 120.f}, {0, 16, 0, 16}},
+                                {15, {99.3f, 106.f, 107.f, 111.f}, {24, 16, 24, 24}},
+                                {19, {104.f, 104.f, 105.f, 109.f}, {16, 0, 0, 16}}};
 // Operands the rings cannot load: the register-staged divisions.
-constexpr TileRate kReg64[] = {{5, {61.6f, 67.9f, 67.8f, 68.f}},
-                               {8, {58.f, 64.5f, 65.f, 66.f}},
-                               {2, {52.5f, 62.4f, 64.5f, 66.8f}},
-                               {3, {46.f, 51.f, 54.f, 55.3f}},
-                               {4, {36.f, 44.f, 47.f, 49.f}}};
-constexpr TileRate kReg32[] = {{5, {116.7f, 126.9f, 128.5f, 129.f}},
-                               {8, {110.7f, 117.f, 119.f, 121.f}},
-                               {2, {81.f, 103.f, 117.f, 124.f}},
-                               {3, {74.9f, 96.1f, 106.5f, 112.f}},
-                               {4, {68.f, 84.f, 92.f, 98.f}}};
+constexpr TileRate kReg64[] = {{5, {61.6f, 67.9f, 67.8f, 68.f}, {24, 24, 24, 24}},
+                               {8, {58.f, 64.5f, 65.f, 66.f}, {24, 24, 24, 24}},
+                               {2, {52.5f, 62.4f, 64.5f, 66.8f}, {32, 32, 24, 24}},
+                               {3, {46.f, 51.f, 54.f, 55.3f}, {24, 24, 16, 16}},
+                               {4, {36.f, 44.f, 47.f, 49.f}, {16, 16, 16, 24}}};
+constexpr TileRate kReg32[] = {{5, {116.7f, 126.9f, 128.5f, 129.f}, {16, 16, 16, 16}},
+                               {8, {110.7f, 117.f, 119.f, 121.f}, {24, 16, 16, 16}},
+                               {2, {81.f, 103.f, 117.f, 124.f}, {16, 8, 0, 8}},
+                               {3, {74.9f, 96.1f, 106.5f, 112.f}, {24, 24, 16, 24}},
+                               {4, {68.f, 84.f, 92.f, 98.f}, {24, 24, 32, 56}}};
 constexpr int64_t kCus = 256;
 
-// Flops per CU of `units` workgroups of one division, over its rate.
+int rate_column(int64_t per_cu) { return per_cu <= 1 ? 0 : per_cu == 2 ? 1 : per_cu <= 5 ? 2 : 3; }
+
+// Flops per CU and k of `units` workgroups of one division, over its rate.
 double division_cost(const TileRate &t, int64_t units) {
   const int64_t per_cu = ceil_div(units, kCus);
-  const float r = t.r[per_cu <= 1 ? 0 : per_cu == 2 ? 1 : per_cu <= 5 ? 2 : 3];
-  return (double)per_cu * kCfgs[t.cfg].bm * kCfgs[t.cfg].bn / r;
+  return (double)per_cu * kCfgs[t.cfg].bm * kCfgs[t.cfg].bn / t.r[rate_column(per_cu)];
 }
 
 int64_t tiles_of(int cfg, int64_t m, int64_t n) {
@@ -146,14 +156,16 @@ bool fits_dispatch(int cfg, int64_t m, int64_t n) {
 // wide and tall panels they re-read twice as often as 64x32 tiles are large.
 // (If no division fits a dispatch, the launch of the one picked says so.)
 template <size_t N>
-const TileRate *best_division(const TileRate (&rates)[N], int64_t m, int64_t n) {
+const TileRate *best_division(const TileRate (&rates)[N], int64_t m, int64_t n, int64_t k) {
   const TileRate *best = nullptr;
   double cost = 0;
   bool fits = false;
   for (const TileRate &t : rates) {
     if (t.cfg == 19 && std::min(m, n) >= 1024) continue;
     const bool f = fits_dispatch(t.cfg, m, n);
-    const double c = division_cost(t, tiles_of(t.cfg, m, n));
+    const int64_t tiles = tiles_of(t.cfg, m, n);
+    const double c = division_cost(t, tiles) *
+                     ((double)k + t.over[rate_column(ceil_div(tiles, kCus))]);
     if (best == nullptr || (f == fits ? c < cost : f)) {
       fits = f;
       best = &t;
@@ -165,10 +177,10 @@ const TileRate *best_division(const TileRate (&rates)[N], int64_t m, int64_t n) 
 
 }  // namespace
 
-int pick_division(int dtype, bool ring, int64_t m, int64_t n) {
+int pick_division(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   const bool f64 = dtype != MG_F32;
-  if (!ring) return (f64 ? best_division(kReg64, m, n) : best_division(kReg32, m, n))->cfg;
-  const int cfg = (f64 ? best_division(kRing64, m, n) : best_division(kRing32, m, n))->cfg;
+  if (!ring) return (f64 ? best_division(kReg64, m, n, k) : best_division(kReg32, m, n, k))->cfg;
+  const int cfg = (f64 ? best_division(kRing64, m, n, k) : best_division(kRing32, m, n, k))->cfg;
   // Between 2^20 and 2^22 outputs the 64x64 and 64x32 tiles run as two k
   // groups of wavefronts where those are as fast: 64x64 tiles that leave a CU
   // at most one (two wavefronts per SIMD instead of one: within 3 % of the
@@ -176,15 +188,14 @@ int pick_division(int dtype, bool ring, int64_t m, int64_t n) {
   // 66.5 TFLOP/s).
   const int64_t outputs = m * n;
   if (outputs >= (int64_t)1 << 20 && outputs < (int64_t)1 << 22) {
-    if (cfg == 23 && tiles_of(23, m, n) <= kCus) return 26;
+    if ((cfg == 23 || cfg == 20) && tiles_of(cfg, m, n) <= kCus) return 26;
     if (cfg == 15 && tiles_of(15, m, n) > 3 * kCus) return 29;
   }
   return cfg;
 }
 
 int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k) {
-  (void)k;
-  return pick_division(dtype, true, m, n);
+  return pick_division(dtype, true, m, n, k);
 }
 
 int gemm_tiles_nn(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alpha,
@@ -231,7 +242,7 @@ PartChoice choose_parts(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   constexpr int64_t kMinK = 1024;           // shorter k: nothing to win
   constexpr int64_t kMaxBytes = 64 << 20;   // of partial sums
   constexpr double kOverK = 64, kLaunchUs = 5, kPlaneGBps = 3500, kHostUs = 26;
-  const int cfg = pick_division(dtype, ring, m, n);
+  const int cfg = pick_division(dtype, ring, m, n, k);
   PartChoice best = {cfg, 1, 0};
   if (k < kMinK) return best;
   const bool f64 = dtype == MG_F64;
@@ -253,7 +264,7 @@ PartChoice choose_parts(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   const double uncut = us(*t1, tiles_of(cfg, m, n), (double)k + kOverK);
   double least = 0.8 * uncut;
   if (least <= kHostUs) return best;
-  const int candidates[2] = {ring ? 23 : 2, ring ? 19 : 4};
+  const int candidates[2] = {ring ? (f64 ? 23 : 20) : 2, ring ? 19 : 4};
   for (int c : candidates) {
     const TileRate *t = find(c);
     const int64_t tiles = tiles_of(c, m, n);
@@ -290,8 +301,8 @@ int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t 
                      const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
                      int64_t ldc, hipStream_t s) {
   const bool ring = ring_operands(dtype, A, lda, B, ldb);
-  PartChoice pc = {pick_division(dtype, ring, m, n), 1, 0};
-  if (m > 0 && n > 0 && alpha != 0.0) pc = choose_parts(dtype, ring, m, n, k);
+  PartChoice pc = choose_parts(dtype, ring, m, n, k);
+  if (alpha == 0.0) pc.parts = 1;
   if (pc.parts > 1) {
     PartPlan pp;
     const int64_t bytes = (int64_t)pc.parts * m * n * (dtype == MG_F64 ? 8 : 4);
@@ -312,7 +323,7 @@ int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t 
     }
     (void)hipGetLastError();
     clear_error();
-    pc.cfg = pick_division(dtype, ring, m, n);
+    pc.cfg = pick_division(dtype, ring, m, n, k);
   }
   return gemm_native_op(dtype, pc.cfg, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
 }

@@ -181,7 +181,7 @@ void launch_batch(Server *S, Lane &L, int64_t batch_id) {
   for (Req *q : direct) {
     const mg_problem &p = q->r.p;
     const int cfg = pick_division(q->r.dtype, ring_operands(q->r.dtype, p.A, p.lda, p.B, p.ldb),
-                                  p.m, p.n);
+                                  p.m, p.n, p.k);
     const int r2 = gemm_native(q->r.dtype, cfg, p.m, p.n, p.k, p.alpha, p.A, p.lda, p.B, p.ldb,
                                p.beta, p.C, p.ldc, L.s);
     if (r2 != MG_OK) q->res.status = r2;

@@ -209,11 +209,38 @@ static void short_ring() {
       }
 }
 
+// Short k: a tile's fill and its C count, so the tile that is fastest per k is
+// not the fastest (times measured, us, beside the cases).
+static void short_k() {
+  struct {
+    int dtype;
+    int64_t m, n, k;
+    const char *kernel;
+  } cases[] = {
+      {MG_F64, 8192, 8192, 64, "gemm_dma_kernel<double, 64, 64,"},     // 128x128 332, 64x64 257
+      {MG_F64, 8192, 8192, 512, "gemm_dma_kernel<double, 64, 64,"},    // 1099, 1020
+      {MG_F64, 4096, 4096, 256, "gemm_dma_kernel<double, 64, 64,"},    // 165, 139
+      {MG_F64, 8192, 8192, 8192, "gemm_dma_kernel<double, 128, 128,"},
+      {MG_F64, 2560, 2560, 64, "gemm_dma_kernel<double, 64, 64,"},     // 64x32 31.5, 64x64 28.9
+      {MG_F64, 256, 1536, 32, "gemm_dma_kernel<double, 32, 32,"},      // 64x32 4.71, 32x32 4.50
+      {MG_F64, 385, 1025, 33, "gemm_native_kernel<double, 32, 32,"},   // 64x32 6.1, 32x32 5.6
+      {MG_F32, 2048, 1536, 512, "gemm_dma_kernel<float, 64, 64, 4, 2,"},  // 2x2: 41.2, 4x2: 33.2
+      {MG_F32, 2048, 2048, 2048, "gemm_dma_kernel<float, 128, 128,"},
+  };
+  for (const auto &c : cases) {
+    launches.clear();
+    EXPECT(mg_gemm(c.dtype, MG_NATIVE, c.m, c.n, c.k, 1.0, fake(1), c.k, fake(2), c.n, 1.0, fake(3),
+                   c.n, nullptr) == MG_OK);
+    EXPECT(launches.size() == 1 && launches[0].kernel.find(c.kernel) != std::string::npos);
+  }
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
   long_rows();
   short_ring();
+  short_k();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
