@@ -31,6 +31,11 @@ int split_layout(int algo, int slices, int64_t m, int64_t n, int64_t k, SplitLay
 int split_prepare(int algo, int slices, int64_t m, int64_t n, int64_t k, const double *A,
                   int64_t lda, const double *B, int64_t ldb, void *ws, hipStream_t s);
 
+// Whether an all-pairs tile of a product of one k segment loads its next stage
+// under the products of the current one.  `batch_tiles`: 64x64 tiles of the
+// whole launch.
+bool split_refill_early(int64_t k, int64_t tiles_m, int64_t tiles_n, int64_t batch_tiles);
+
 // Work divisions of the product kernel; cfg < 0 picks by size.
 int split_num_cfgs();
 // `latency`: one call on an otherwise idle device (the all-pairs 64x64 tile at

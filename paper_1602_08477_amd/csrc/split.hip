@@ -414,6 +414,7 @@ struct SplitArgs {
   int64_t kp_bytes;  // row pitch of a slice in bytes
   int s, bits;
   int seg_stages, total_stages;
+  int early = 0;  // all-pairs tile: refill under the products (split_refill_early)
   double alpha, beta;
 };
 
@@ -1443,25 +1444,10 @@ __device__ __forceinline__ void split_allpairs_tile(const SplitArgs &a, int m0, 
   store_block<FMW, FNW>(a, part, m0 + wm0 + 4 * g, n0 + wn0 + l16);
 }
 
-// When a place is refilled early.  Workgroups whose loads are hidden drift
-// apart over a large product and stop sharing slices in their XCD's L2 (INT8
-// n = 4096: 85 M L2 misses a launch against 24 M, 1.71 against 1.52 ms); with
-// the loads exposed the ones ahead wait for memory and the ones behind catch
-// up from L2.  So: up to 2048 tiles (four rounds of 512 workgroups), or while
-// the slices of the 8x8 tiles that an XCD works on, all their k, fit its L2
-// (4 MB).  Whole calls, early against late: INT8 n = 512 / 1024 / 1536 / 2500
-// 29.0 / 46.3 / 124 / 431 against 32.6 / 55.2 / 139 / 449 us, n = 3000 / 4096
-// 761 / 1858 against 725 / 1649, 4096 x 4096 x 512 217 against 239; BF16
-// n = 1024 / 2500 / 4096 65 / 688 / 3073 against 86 / 744 / 2866.
-constexpr int kEarlyTiles = 2048;
-constexpr int64_t kXcdL2 = 4 << 20;
-
 template <int ALGO, int S, typename Off>
 __device__ __forceinline__ void split_allpairs_any(const SplitArgs &a, int m0, int n0,
                                                    unsigned char *lds) {
-  const int64_t tiles = (int64_t)((a.m + 63) >> 6) * ((a.n + 63) >> 6);
-  const bool shared = tiles > kEarlyTiles && a.kp_bytes * (S * 16 * 64) > kXcdL2;
-  if (!shared && a.seg_stages >= a.total_stages)
+  if (a.early)
     split_allpairs_tile<ALGO, S, true, Off>(a, m0, n0, lds);
   else
     split_allpairs_tile<ALGO, S, false, Off>(a, m0, n0, lds);
@@ -1529,7 +1515,7 @@ int launch_batched_t(const SplitArgs *d_args, const SplitPrepDesc *d_desc, const
 // slice pitches mp, np; the partial-sum region unused); only the tiles that
 // hold outputs run.  `a` counts 128-byte stages.
 template <int ALGO>
-int launch_allpairs_t(const SplitArgs &a128, hipStream_t s) {
+int launch_allpairs_t(const SplitArgs &a128, int64_t k, hipStream_t s) {
   constexpr int S = batch_slices(ALGO);
   typedef AllPairsShape<S> SH;
   if (a128.s != S) {
@@ -1543,6 +1529,8 @@ int launch_allpairs_t(const SplitArgs &a128, hipStream_t s) {
   a.total_stages = a128.total_stages * (kStageBytes / SH::SB);
   a.seg_stages = a128.seg_stages * (kStageBytes / SH::SB);
   const int tiles_m = (int)ceil_div(a.m, SH::BM), tiles_n = (int)ceil_div(a.n, SH::BN);
+  a.early = a.seg_stages >= a.total_stages &&
+            split_refill_early(k, tiles_m, tiles_n, (int64_t)tiles_m * tiles_n);
   hipLaunchKernelGGL(kern, dim3((unsigned)(tiles_m * tiles_n)), dim3(SH::THREADS), SH::LDS_BYTES,
                      s, a, tiles_m, tiles_n);
   MG_HIP_TRY(hipGetLastError());
@@ -1695,6 +1683,28 @@ int split_prepare(int algo, int slices, int64_t m, int64_t n, int64_t k, const d
   return MG_OK;
 }
 
+// Workgroups whose loads are hidden drift apart over a long k and stop sharing
+// slices in their XCD's L2 (INT8 n = 4096: 85 M L2 misses a launch against 24 M);
+// with the loads exposed the ones ahead wait for memory and the ones behind
+// catch up from L2.  So k bounds the early refill: up to 2048 it wins at every
+// size (whole calls, early against late: INT8 n = 1024 / 2048 / 4096, k = 2048: 75
+// / 195 / 731 against 93 / 200 / 778 us; BF16 1536 x 2048 x 2048 273 against
+// 317), beyond it loses where many workgroups share both operands (INT8 k =
+// 8192, n = 2048 / 2816 / 2048 x 4096: 973 / 1845 / 2308 against 881 / 1659 /
+// 1678).  It still wins for long k where one round of 512 workgroups, and half
+// of another, takes the whole product (n = 1024, k = 8192: 266 against 339), and
+// where one operand is so narrow that its panels stay in L2 whatever the others
+// do (768 x 5461 x 4096: 519 against 565).  In a batch the other problems' tiles
+// count too (16 of 1024 x 1024 x 4096: 2347 against 2167; 3 of them: 420 against
+// 462) unless a problem's own are few (500 of 128 x 128 x 4096: 3211 against
+// 3409).
+bool split_refill_early(int64_t k, int64_t tiles_m, int64_t tiles_n, int64_t batch_tiles) {
+  const int64_t tiles = tiles_m * tiles_n;
+  if (k <= 2048) return true;
+  if (batch_tiles > 1536) return tiles <= 16;
+  return tiles <= 768 || std::min(tiles_m, tiles_n) <= 12;
+}
+
 int split_num_cfgs() { return 17; }
 
 // Product-kernel work division (measured on MI355X at n = 4096): the 256x256
@@ -1788,8 +1798,8 @@ int split_multiply(int algo, int slices, int64_t m, int64_t n, int64_t k, double
     case 13: return launch_split_dma<2, 2, 4, 4, 2, 128>(algo, a, L, s);  // 128x128, 4 waves, 2 x 128 B
     case 14: return launch_split_dma<2, 4, 4, 2, 3, 128>(algo, a, L, s);  // 128x128, 8 waves, 3 x 128 B
     case 16:  // all-pairs 64x64 tile, one LDS stage, two workgroups per CU
-      return algo == MG_SPLIT_BF16 ? launch_allpairs_t<MG_SPLIT_BF16>(a, s)
-                                   : launch_allpairs_t<MG_SPLIT_I8>(a, s);
+      return algo == MG_SPLIT_BF16 ? launch_allpairs_t<MG_SPLIT_BF16>(a, k, s)
+                                   : launch_allpairs_t<MG_SPLIT_I8>(a, k, s);
     case 15: {  // pair-parallel: groups of slice pairs x 128x128 tiles, then the fold
       if (!pairs_eligible(L.mp, L.np)) {
         set_error("split work division 15 serves shapes with fewer than %lld tiles of 128x128",
@@ -2136,6 +2146,8 @@ int gemm_split_batched(int algo, int64_t count, const mg_problem *probs, hipStre
   }
   unsigned char *w = static_cast<unsigned char *>(dev);
   const int bits = split_bits(algo);
+  int64_t batch_tiles = 0;
+  for (const BLayout &l : L) batch_tiles += (l.mr / TILE) * (l.nr / TILE);
   for (int j = 0; j < nl; ++j) {
     const mg_problem &q = probs[live[(size_t)j]];
     const BLayout &l = L[(size_t)j];
@@ -2159,6 +2171,8 @@ int gemm_split_batched(int algo, int64_t count, const mg_problem *probs, hipStre
     // stage counts in the all-pairs tile's 64-byte stages
     a.total_stages = (int)(a.kp_bytes / 64);
     a.seg_stages = (int)std::min<int64_t>(seg * (kStageBytes / 64), a.total_stages);
+    a.early = a.seg_stages >= a.total_stages &&
+              split_refill_early(q.k, l.mr / TILE, l.nr / TILE, batch_tiles);
     a.alpha = q.alpha;
     a.beta = q.beta;
     SplitPrepDesc &d = desc[(size_t)j];

@@ -18,6 +18,10 @@
 
 #include "mg.h"
 
+namespace mg {  // internal to the library, exported
+bool split_refill_early(int64_t k, int64_t tiles_m, int64_t tiles_n, int64_t batch_tiles);
+}
+
 static int failures = 0;
 
 #define EXPECT(cond)                                                              \
@@ -235,12 +239,41 @@ static void short_k() {
   }
 }
 
+// The all-pairs split tile's refill (times measured, us, early / late).
+static void split_refill() {
+  struct {
+    int64_t k, tm, tn, batch;
+    bool early;
+  } cases[] = {
+      {1024, 16, 16, 256, true},     // 46 / 53
+      {8192, 16, 16, 256, true},     // 266 / 339
+      {8192, 24, 24, 576, true},     // 626 / 675
+      {2048, 32, 32, 1024, true},    // 195 / 200
+      {4096, 32, 32, 1024, false},   // 408 / 394
+      {8192, 32, 32, 1024, false},   // 973 / 881
+      {8192, 16, 64, 1024, false},   // 1066 / 930
+      {4096, 12, 86, 1032, true},    // 519 / 565
+      {2048, 44, 44, 1936, true},    // 345 / 365
+      {4096, 44, 44, 1936, false},   // 778 / 720
+      {8192, 32, 64, 2048, false},   // 2308 / 1678
+      {2048, 64, 64, 4096, true},    // 731 / 778
+      {4096, 64, 64, 4096, false},   // 1824 / 1517
+      {4096, 16, 16, 768, true},     // three problems in a batch: 420 / 462
+      {4096, 16, 16, 4096, false},   // sixteen: 2347 / 2167
+      {4096, 2, 2, 2000, true},      // 500 of 4 tiles: 3211 / 3409
+      {2048, 12, 12, 9216, true},    // 2797 / 2916
+  };
+  for (const auto &c : cases)
+    EXPECT(mg::split_refill_early(c.k, c.tm, c.tn, c.batch) == c.early);
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
   long_rows();
   short_ring();
   short_k();
+  split_refill();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
