@@ -114,8 +114,8 @@ int mg_gemm_cfg(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alph
                 double beta, void *C, int64_t ldc, void *stream);
 
 /* The cfg mg_gemm picks for this shape (its work-division rule) when A and B
- * have 16-byte aligned rows and pitches under 16 MiB, which the direct-load
- * rings need; for other operands it picks among the register-staged divisions
+ * have 16-byte aligned rows and pitches under 16 MiB (128 MiB for B, and for
+ * A stored k x m), which the direct-load rings need; for other operands it picks among the register-staged divisions
  * by the same rule. */
 int mg_pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
 

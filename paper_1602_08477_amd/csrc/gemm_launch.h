@@ -125,8 +125,8 @@ int launch_dma(const GemmArgs<T> &g, const KSplit<T> &ks, hipStream_t s) {
 }
 
 // Work divisions 0-13 stage A and B through registers; 14-24 load them
-// straight into an LDS ring (A and B 16-byte aligned, pitches under 16 MiB:
-// otherwise a register-staged division of the same macro-tile runs); 25 is the naive
+// straight into an LDS ring (operands as ring_operands says: otherwise a
+// register-staged division of the same macro-tile runs); 25 is the naive
 // one-output-per-lane mapping; 26-29 are direct-load rings whose wavefronts
 // form two k groups (twice the wavefronts per output block).  The host's table
 // of shapes (kCfgs in gemm_native.hip) lists the same divisions in order.
@@ -234,7 +234,7 @@ int gemm_tiles_t(int cfg, int64_t m, int64_t n, int64_t k, double alpha, const v
   g.k = (int)k;
   g.alpha = (T)alpha;
   g.beta = (T)beta;
-  const bool dma_ok = ring_operands(sizeof(T) == 8 ? MG_F64 : MG_F32, A, lda, B, ldb);
+  const bool dma_ok = ring_operands(sizeof(T) == 8 ? MG_F64 : MG_F32, TA, TB, A, lda, B, ldb);
   const KSplit<T> ks = {static_cast<T *>(pp.planes), pp.parts, pp.kpart};
   return launch_cfg<T, TA, TB>(cfg, dma_ok, g, ks, s);
 }

@@ -15,10 +15,11 @@ int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads);
 int pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
 // The same for either kind of operands (`ring`: ring_operands of A and B).
 int pick_division(int dtype, bool ring, int64_t m, int64_t n, int64_t k);
-// True if the direct-load rings can load A and B: 16-byte aligned rows, and
-// pitches whose tile offsets fit the rings' 32-bit lane offsets (255 pitches
-// plus a row of the tile).
-bool ring_operands(int dtype, const void *A, int64_t lda, const void *B, int64_t ldb);
+// True if the direct-load rings can load A and B (stored transposed when ta /
+// tb): 16-byte aligned rows, and pitches whose tile offsets fit the rings'
+// 32-bit lane offsets.
+bool ring_operands(int dtype, bool ta, bool tb, const void *A, int64_t lda, const void *B,
+                   int64_t ldb);
 
 // How a product's k range is cut over workgroups (parts == 1: not): `parts`
 // ranges of `kpart` k, partial sums in `planes` (parts x m x n elements).

@@ -180,8 +180,8 @@ void launch_batch(Server *S, Lane &L, int64_t batch_id) {
     if (q->r.algo == MG_NATIVE && rc != MG_OK) q->res.status = rc;
   for (Req *q : direct) {
     const mg_problem &p = q->r.p;
-    const int cfg = pick_division(q->r.dtype, ring_operands(q->r.dtype, p.A, p.lda, p.B, p.ldb),
-                                  p.m, p.n, p.k);
+    const bool ring = ring_operands(q->r.dtype, false, false, p.A, p.lda, p.B, p.ldb);
+    const int cfg = pick_division(q->r.dtype, ring, p.m, p.n, p.k);
     const int r2 = gemm_native(q->r.dtype, cfg, p.m, p.n, p.k, p.alpha, p.A, p.lda, p.B, p.ldb,
                                p.beta, p.C, p.ldc, L.s);
     if (r2 != MG_OK) q->res.status = r2;

@@ -267,6 +267,26 @@ static void split_refill() {
     EXPECT(mg::split_refill_early(c.k, c.tm, c.tn, c.batch) == c.early);
 }
 
+// Which operands the rings load: aligned rows, and pitches whose lane offsets
+// fit 32 bits (255 rows along k, 31 rows of k).
+static void ring_pitches() {
+  for (int dtype : {MG_F64, MG_F32})
+    for (int ta : {0, 1})
+      for (int tb : {0, 1})
+        for (int64_t a : {0, 1, 2})
+          for (int64_t b : {0, 1, 2}) {
+            const int64_t esz = dtype == MG_F64 ? 8 : 4;
+            const int64_t pitch[3] = {(1ll << 24) / esz - 16, (1ll << 27) / esz - 16,
+                                      (1ll << 27) / esz};
+            launches.clear();
+            EXPECT(mg_gemm_ex(dtype, -1, ta, tb, 64, 64, 64, 1.0, fake(1), pitch[a], fake(2),
+                              pitch[b], 1.0, fake(3), 64, nullptr) == MG_OK);
+            const bool ring = a <= (ta ? 1 : 0) && b <= (tb ? 0 : 1);
+            EXPECT(launches.size() == 1 &&
+                   (launches[0].kernel.find("gemm_dma_kernel<") != std::string::npos) == ring);
+          }
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
@@ -274,6 +294,7 @@ int main() {
   short_ring();
   short_k();
   split_refill();
+  ring_pitches();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
