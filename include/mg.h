@@ -84,8 +84,12 @@ int mg_build_flags(void);
  * sums its k range in the order of a one-k-group work division into a
  * workspace (at most 64 MiB) from the library's stream-ordered pool, and a
  * second kernel adds the parts in order (deterministic; within the rounding
- * bound of the uncut sum, not its bits).  While `stream` is being captured, or
- * if the pool cannot give the workspace, the product runs uncut.  The split
+ * bound of the uncut sum, not its bits).  Whether and how depends on the type,
+ * the extents and whether the operands have the aligned rows that
+ * mg_pick_tile_cfg names, so the same values at another alignment, pitch or
+ * layout may be summed in other parts.  While `stream` is being captured, if it
+ * belongs to another device than the current one, or if the pool cannot give
+ * the workspace, the product runs uncut.  The split
  * algorithms use the
  * default slice count (mg_split_default_slices) and take their workspace
  * from the library's stream-ordered workspace pool on `stream` (released on
@@ -115,8 +119,8 @@ int mg_gemm_cfg(int dtype, int cfg, int64_t m, int64_t n, int64_t k, double alph
 
 /* The cfg mg_gemm picks for this shape (its work-division rule) when A and B
  * have 16-byte aligned rows and pitches under 16 MiB (128 MiB for B, and for
- * A stored k x m), which the direct-load rings need; for other operands it picks among the register-staged divisions
- * by the same rule. */
+ * A stored k x m), which the direct-load rings need; for other operands it
+ * picks among the register-staged divisions by the same rule. */
 int mg_pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
 
 /* mg_gemm_ex: C <- alpha*op(A)*op(B) + beta*C on the native kernels, with

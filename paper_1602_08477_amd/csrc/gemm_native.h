@@ -31,8 +31,8 @@ struct PartPlan {
 // mg_gemm's route for operands of any kind (arguments already validated): the
 // picked division, with k cut into parts where the output has too few tiles
 // for the chip and k is long.  The partial sums' workspace comes from the
-// stream-ordered pool; under stream capture, or when the pool cannot give it,
-// the product runs uncut.
+// stream-ordered pool; under stream capture, on a stream of another device, or
+// when the pool cannot give it, the product runs uncut.
 int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double alpha,
                      const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
                      int64_t ldc, hipStream_t s);

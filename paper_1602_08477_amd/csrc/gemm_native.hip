@@ -303,6 +303,22 @@ int add_parts(const PartPlan &pp, int64_t m, int64_t n, double alpha, double bet
 
 }  // namespace
 
+namespace {
+
+// Whether a cut call may take its workspace: not while `s` is captured, and only
+// for a stream of the current device (the pool's memory is that device's, and a
+// stream of another one may not reach it).
+bool may_cut_on(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = 0;
+  hipDevice_t stream_dev = 0;
+  return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+         hipGetDevice(&dev) == hipSuccess && hipStreamGetDevice(s, &stream_dev) == hipSuccess &&
+         stream_dev == dev;
+}
+
+}  // namespace
+
 int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double alpha,
                      const void *A, int64_t lda, const void *B, int64_t ldb, double beta, void *C,
                      int64_t ldc, hipStream_t s) {
@@ -312,9 +328,7 @@ int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t 
   if (pc.parts > 1) {
     PartPlan pp;
     const int64_t bytes = (int64_t)pc.parts * m * n * (dtype == MG_F64 ? 8 : 4);
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        pool_alloc(&pp.planes, bytes, s) == MG_OK) {
+    if (may_cut_on(s) && pool_alloc(&pp.planes, bytes, s) == MG_OK) {
       pp.parts = pc.parts;
       pp.kpart = pc.kpart;
       auto run = ta ? (tb ? gemm_tiles_tt : gemm_tiles_tn) : (tb ? gemm_tiles_nt : gemm_tiles_nn);

@@ -37,8 +37,16 @@ static int failures = 0;
 struct Launch {
   std::string kernel;
   dim3 grid, block;
-  std::vector<std::vector<unsigned char>> args;  // the first 16 bytes of each
+  struct {  // of a product's kernel: the workspace, parts and k per part
+    void *planes;
+    int parts, kpart;
+  } cut;
 };
+static struct {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  bool pool_empty = false;
+  int stream_device = 0;
+} state;
 static std::vector<Launch> launches;
 static std::map<const void *, std::string> &kernels() {
   static std::map<const void *, std::string> m;  // filled by static constructors
@@ -80,8 +88,21 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
   *s = config.s;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **, size_t, hipStream_t) {
-  launches.push_back({kernels()[f], grid, block, {}});
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t,
+                           hipStream_t) {
+  Launch l = {kernels()[f], grid, block, {}};
+  if (l.kernel.find("gemm_dma_kernel<") != std::string::npos ||
+      l.kernel.find("gemm_native_kernel<") != std::string::npos)
+    std::memcpy(&l.cut, args[3], sizeof l.cut);
+  launches.push_back(l);
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+  *s = state.capture;
+  return hipSuccess;
+}
+hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t *d) {
+  *d = state.stream_device;
   return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
@@ -110,6 +131,7 @@ hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
 }
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
 hipError_t hipMallocFromPoolAsync(void **p, size_t, hipMemPool_t, hipStream_t) {
+  if (state.pool_empty) return hipErrorOutOfMemory;
   *p = fake(91);
   return hipSuccess;
 }
@@ -287,6 +309,48 @@ static void ring_pitches() {
           }
 }
 
+// Products cut along k: the parts cover k, the grid holds every tile of every
+// part, and a second kernel adds them; uncut on a stream that is captured or
+// belongs to another device, and when the pool has no memory.
+static void long_k() {
+  struct {
+    int64_t m, n, k;
+  } shapes[] = {{64, 64, 16384}, {1, 3, 20001}, {65, 33, 9985}, {130, 70, 8193}, {200, 200, 12288},
+                {96, 80, 16384},
+                // a last part of one k: on the FP64 rings, and off the rings
+                {33, 70, 19041}, {33, 70, 12097}, {33, 70, 16193}};
+  int last_of_one = 0;
+  for (int dtype : {MG_F64, MG_F32})
+    for (int64_t odd : {0, 1})  // pitches that the rings load, and not
+      for (int t = 0; t < 4; ++t)
+        for (const auto &q : shapes) {
+          auto run = [&] {
+            launches.clear();
+            return mg_gemm_ex(dtype, -1, t & 1, t >> 1, q.m, q.n, q.k, 1.5, fake(1), 20480 + odd,
+                              fake(2), 20480 + odd, 0.5, fake(3), q.n, nullptr);
+          };
+          EXPECT(run() == MG_OK && launches.size() == 2);
+          if (launches.size() != 2) continue;
+          const Launch cut = launches[0];
+          const int64_t parts = cut.cut.parts, kpart = cut.cut.kpart;
+          EXPECT(cut.cut.planes == fake(91) && parts >= 2);
+          EXPECT((parts - 1) * kpart < q.k && q.k <= parts * kpart && cut.grid.x % parts == 0);
+          EXPECT(launches[1].kernel.find("add_parts_kernel<") != std::string::npos);
+          last_of_one += q.k - (parts - 1) * kpart == 1;
+          for (int why = 0; why < 3; ++why) {
+            state.capture = why == 0 ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+            state.stream_device = why == 1;
+            state.pool_empty = why == 2;
+            EXPECT(run() == MG_OK && launches.size() == 1);
+            EXPECT(std::strlen(mg_last_error()) == 0);
+            if (launches.size() == 1)
+              EXPECT(launches[0].cut.planes == nullptr && launches[0].cut.parts == 1);
+          }
+          state = {};
+        }
+  EXPECT(last_of_one >= 12);  // each of the three, in every layout
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
@@ -295,6 +359,7 @@ int main() {
   short_k();
   split_refill();
   ring_pitches();
+  long_k();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
