@@ -201,11 +201,14 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, ks, s)
                     : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
     case 25: return launch_naive<T, TA, TB>(g, s);
-    case 26:
-      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 2, TA, TB, 2, 2>(g, ks, s)
+    case 26:  // three stages of one k-step, three workgroups per CU, against two of
+              // two and two: FP32 n = 4096 A^T B 1268 -> 1161 us, A B^T 1202 -> 1132, A B
+              // 1145 -> 1139 (n = 1024 21.2 -> 21.6); FP64 1944 -> 1920
+      return dma_ok ? launch_dma<T, 64, 64, 2, 2, 3, TA, TB, 2>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
-    case 27:
-      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 2, TA, TB, 2>(g, ks, s)
+    case 27:  // three stages: one workgroup per CU by its registers, so two hide
+              // less (FP64 n = 4096 2.53 -> 2.14 ms, FP32 1.20 -> 1.11)
+      return dma_ok ? launch_dma<T, 128, 64, 2, 2, 3, TA, TB, 2>(g, ks, s)
                     : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 28:
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 4, TA, TB, 2>(g, ks, s)
