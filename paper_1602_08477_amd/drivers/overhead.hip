@@ -153,8 +153,8 @@ void one_shape(int n, int reps, hipStream_t s, bool first) {
     };
   } else if (cfg == 19 || cfg == 23 || cfg == 21 || cfg == 26) {
     if (cfg == 26) {
-      typedef mg::DmaShape<double, 64, 64, 2, 2, 2, 2, 2> S;
-      auto k = mg::gemm_dma_kernel<double, 64, 64, 2, 2, 2, false, false, 2, 2>;
+      typedef mg::DmaShape<double, 64, 64, 2, 2, 3, 2> S;
+      auto k = mg::gemm_dma_kernel<double, 64, 64, 2, 2, 3, false, false, 2>;
       CK(hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES));
       raw = [&, tm, tn, k] { direct(k, dim3(tm * tn), S::THREADS, S::LDS_BYTES, g, tm, tn, s); };
