@@ -143,12 +143,16 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
   constexpr int KU32 = F64 ? 1 : 2;
   // 128x128 tiles on 16 wavefronts (13, the FP64 ring 21 and what 17, 21 and 22
   // fall back to) run on 8 where 16 would be more work-items than a dispatch
-  // holds: the same sums.
+  // holds: the same sums.  Register-staged ones of A^T B always do: their
+  // fragments do not fit 16 wavefronts' registers (n = 4096 FP64 3011 -> 1986 us,
+  // FP32 1271 -> 1034; the other layouts lose by it, A B^T 1936 -> 1992).
   const bool many = ((int64_t)g.m + 127) / 128 * (((int64_t)g.n + 127) / 128) * 1024 >
                     (int64_t)UINT32_MAX;
   auto reg128 = [&] {
-    return many ? launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, ks, s)
-                : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
+    if constexpr (TA && !TB) return launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, ks, s);
+    else
+      return many ? launch_one<T, 128, 128, 4, 2, 1, TA, TB>(g, ks, s)
+                  : launch_one<T, 128, 128, 4, 4, 1, TA, TB>(g, ks, s);
   };
   switch (cfg) {
     case 0: return launch_one<T, 128, 128, 2, 2, 1, TA, TB>(g, ks, s);
