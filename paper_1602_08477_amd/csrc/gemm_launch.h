@@ -181,8 +181,11 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
     case 17:
       return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s) : reg128();
     case 18:
-      return dma_ok ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
-                    : launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
+      if (!dma_ok) return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
+      // FP32 on 8 wavefronts: on 16 the transposed layouts are register bound
+      // (n = 4096 A B^T 1105 -> 1026 us, A^T B 1236 -> 1043; A B 1004 -> 1016)
+      return F64 ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
+                 : launch_dma<T, 256, 128, 2, 4, 3, TA, TB>(g, ks, s);
     case 19:
       if (!dma_ok) return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
       return g.k < DmaShape<T, 32, 32, 2, 2, 4>::LOOP_K

@@ -76,8 +76,9 @@ int tile_cfg_info(int dtype, int cfg, int *bm, int *bn, int *bk, int *threads) {
   }
   if (bk) *bk = kCfgs[cfg].bkm * (dtype == MG_F64 ? Mfma<double>::BK : Mfma<float>::BK);
   if (threads)
-    *threads = cfg == 21 && dtype == MG_F64 ? 1024  // 16 wavefronts (launch_cfg)
-                                            : 64 * kCfgs[cfg].wgm * kCfgs[cfg].wgn * kCfgs[cfg].ks;
+    *threads = cfg == 21 && dtype == MG_F64   ? 1024  // 16 wavefronts (launch_cfg)
+               : cfg == 18 && dtype == MG_F32 ? 512
+                                              : 64 * kCfgs[cfg].wgm * kCfgs[cfg].wgn * kCfgs[cfg].ks;
   return MG_OK;
 }
 

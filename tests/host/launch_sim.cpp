@@ -351,6 +351,28 @@ static void long_k() {
   EXPECT(last_of_one >= 12);  // each of the three, in every layout
 }
 
+// Workgroups of the explicit divisions whose shape depends on type or layout.
+static void explicit_divisions() {
+  struct {
+    int dtype, cfg, ta, tb;
+    int64_t odd;
+    unsigned threads;
+  } cases[] = {
+      {MG_F64, 13, 0, 0, 0, 1024}, {MG_F64, 13, 1, 0, 0, 512}, {MG_F64, 13, 1, 1, 0, 1024},
+      {MG_F32, 13, 1, 0, 0, 512},  {MG_F64, 21, 1, 0, 1, 512}, {MG_F64, 21, 1, 0, 0, 1024},
+      {MG_F64, 18, 0, 1, 0, 1024}, {MG_F32, 18, 0, 1, 0, 512}, {MG_F32, 26, 1, 0, 0, 512},
+  };
+  for (const auto &c : cases) {
+    launches.clear();
+    EXPECT(mg_gemm_ex(c.dtype, c.cfg, c.ta, c.tb, 300, 300, 300, 1.0, fake(1), 304 + c.odd, fake(2),
+                      304 + c.odd, 1.0, fake(3), 300, nullptr) == MG_OK);
+    EXPECT(launches.size() == 1 && launches[0].block.x == c.threads);
+    int threads = 0;
+    EXPECT(mg_tile_cfg_info(c.dtype, c.cfg, nullptr, nullptr, nullptr, &threads) == MG_OK);
+    EXPECT(c.odd || (c.cfg == 13 && c.ta && !c.tb) || threads == (int)c.threads);
+  }
+}
+
 int main() {
   split_batch_offsets();
   batch_dispatches();
@@ -360,6 +382,7 @@ int main() {
   split_refill();
   ring_pitches();
   long_k();
+  explicit_divisions();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
