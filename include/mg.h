@@ -131,7 +131,7 @@ int mg_pick_tile_cfg(int dtype, int64_t m, int64_t n, int64_t k);
  * plain layout (bit-identical results for the same cfg).
  *   transa 0: A stored m x k, lda >= k;  1: A stored k x m, lda >= m.
  *   transb 0: B stored k x n, ldb >= n;  1: B stored n x k, ldb >= k.
- *   cfg    a work division as in mg_gemm_cfg, or -1 for mg_gemm's choice.
+ *   cfg    a work division as in mg_gemm_cfg, or -1 for the library's choice.
  *   dtype  MG_F64 or MG_F32.  Other arguments, special cases and errors as
  *          mg_gemm (MG_ERR_INVALID_ARG for trans flags other than 0/1). */
 int mg_gemm_ex(int dtype, int cfg, int transa, int transb, int64_t m, int64_t n, int64_t k,

@@ -127,6 +127,8 @@ constexpr TileRate kRing32[] = {{22, {120.6f, 130.1f, 131.5f, 133.f}, {0, 0, 8, 
                                 {20, {118.f, 113.f, 117.f, 120.f}, {0, 16, 0, 16}},
                                 {15, {99.3f, 106.f, 107.f, 111.f}, {24, 16, 24, 24}},
                                 {19, {104.f, 104.f, 105.f, 109.f}, {16, 0, 0, 16}}};
+// The FP32 64x64 tiles of products cut along k, which leave a CU at most two.
+constexpr TileRate kCutTile32 = {23, {106.7f, 110.7f, 115.f, 119.f}, {}};
 // Operands the rings cannot load: the register-staged divisions.
 constexpr TileRate kReg64[] = {{5, {61.6f, 67.9f, 67.8f, 68.f}, {24, 24, 24, 24}},
                                {8, {58.f, 64.5f, 65.f, 66.f}, {24, 24, 24, 24}},
@@ -255,6 +257,7 @@ PartChoice choose_parts(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   const bool f64 = dtype == MG_F64;
   const int64_t esz = f64 ? 8 : 4, bk = 128 / esz, steps = ceil_div(k, bk);
   auto find = [&](int c) -> const TileRate * {
+    if (ring && !f64 && c == kCutTile32.cfg) return &kCutTile32;
     auto in = [&](const auto &tab) -> const TileRate * {
       for (const TileRate &t : tab)
         if (t.cfg == c) return &t;
@@ -271,7 +274,7 @@ PartChoice choose_parts(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   const double uncut = us(*t1, tiles_of(cfg, m, n), (double)k + kOverK);
   double least = 0.8 * uncut;
   if (least <= kHostUs) return best;
-  const int candidates[2] = {ring ? (f64 ? 23 : 20) : 2, ring ? 19 : 4};
+  const int candidates[2] = {ring ? 23 : 2, ring ? 19 : 4};
   for (int c : candidates) {
     const TileRate *t = find(c);
     const int64_t tiles = tiles_of(c, m, n);
@@ -318,6 +321,14 @@ bool may_cut_on(hipStream_t s) {
          stream_dev == dev;
 }
 
+// The division for A B^T in place of `cfg`, with the same sums: FP32 64x64 tiles
+// on 4 wavefronts (23) where one or two of them share a CU, or four and more: on
+// 8 (20) each wavefront reads 16 columns of B^T for half the rows (1024 x 1024 x
+// 3616 76 against 64 us).  Three per CU stay (2048 x 1536 x 256 20 against 23 us).
+int division_nt(int cfg, int64_t tiles) {
+  return cfg == 20 && ceil_div(tiles, kCus) != 3 ? 23 : cfg;
+}
+
 }  // namespace
 
 int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t k, double alpha,
@@ -326,6 +337,7 @@ int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t 
   const bool ring = ring_operands(dtype, ta, tb, A, lda, B, ldb);
   PartChoice pc = choose_parts(dtype, ring, m, n, k);
   if (alpha == 0.0) pc.parts = 1;
+  if (!ta && tb) pc.cfg = division_nt(pc.cfg, tiles_of(pc.cfg, m, n));
   if (pc.parts > 1) {
     PartPlan pp;
     const int64_t bytes = (int64_t)pc.parts * m * n * (dtype == MG_F64 ? 8 : 4);
@@ -345,6 +357,7 @@ int gemm_native_auto(int dtype, bool ta, bool tb, int64_t m, int64_t n, int64_t 
     (void)hipGetLastError();
     clear_error();
     pc.cfg = pick_division(dtype, ring, m, n, k);
+    if (!ta && tb) pc.cfg = division_nt(pc.cfg, tiles_of(pc.cfg, m, n));
   }
   return gemm_native_op(dtype, pc.cfg, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, s);
 }

@@ -351,6 +351,25 @@ static void long_k() {
   EXPECT(last_of_one >= 12);  // each of the three, in every layout
 }
 
+// FP32 A B^T: 64x64 tiles on 4 wavefronts unless three share a CU (times measured,
+// us: 8 / 4 wavefronts).
+static void f32_nt() {
+  struct {
+    int64_t m, n, k;
+    const char *kernel;
+  } cases[] = {{1000, 1000, 512, " 64, 64, 2, 2, 2,"},    // k = 1024: 24.3 / 20.9
+               {2048, 1536, 512, " 64, 64, 4, 2, 4,"},    // k = 256: 19.8 / 23.0
+               {64, 64, 16384, nullptr}};                 // cut along k: 4 wavefronts
+  for (const auto &c : cases) {
+    launches.clear();
+    EXPECT(mg_gemm_ex(MG_F32, -1, 0, 1, c.m, c.n, c.k, 1.0, fake(1), c.k, fake(2), c.k, 1.0, fake(3),
+                      c.n, nullptr) == MG_OK);
+    EXPECT(launches.size() == (c.kernel ? 1u : 2u));
+    EXPECT(c.kernel == nullptr || launches[0].kernel.find(c.kernel) != std::string::npos);
+    EXPECT(c.kernel || launches[0].kernel.find(" 64, 64, 4, 2, 4,") == std::string::npos);
+  }
+}
+
 // Workgroups of the explicit divisions whose shape depends on type or layout.
 static void explicit_divisions() {
   struct {
@@ -383,6 +402,7 @@ int main() {
   ring_pitches();
   long_k();
   explicit_divisions();
+  f32_nt();
   std::printf("host launches: %d failures\n", failures);
   return failures != 0;
 }
