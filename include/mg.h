@@ -399,9 +399,11 @@ int mg_gemm_batched_noalloc(int dtype, int64_t count, const mg_problem *probs, v
  * Batches on different streams run concurrently on the
  * device (the paper's scheduler may run grids from several streams in
  * parallel, Section 3.3); requests that arrive while batches run are admitted
- * as slots and bytes free up and go out with the next batch.  A request's
- * arithmetic depends only on its own shape (fixed tile class table), so its
- * result is the same alone or in any mix.
+ * as slots and bytes free up and go out with the next batch.  Native requests
+ * of 1024^3 multiply-adds and more run as mg_gemm's uncut product (k is never
+ * cut here, so a few-tile product with a long k takes longer than mg_gemm's).
+ * A request's arithmetic depends only on its own shape and operands' alignment
+ * (fixed tile class table), so its result is the same alone or in any mix.
  * The caller keeps every operand alive and unmodified until the request is
  * reported done; the library never copies operands.
  * Timestamps are steady-clock nanoseconds (mg_now_ns). */

@@ -16,7 +16,8 @@
 // So scalar registers carry the addresses, the loop is unrolled over the ring
 // (constant LDS addresses, no branches), and wavefronts with up to 2x2
 // blocks read the fragments of a half step while the previous half step's
-// products run.  FP64, k = 2048, by tiles per CU, before -> after: 64x64
+// products run.  FP64, k = 2048, by tiles per CU, before -> after (whole calls;
+// the division rule's rates have the launch taken off): 64x64
 // 1: 48.7 -> 64.6, 4: 65.2 -> 70.8, 16: 66.5 -> 72 TFLOP/s; 32x32 1: 25.2 ->
 // 53.5, 12: 52 -> 64; 128x128 (now on 16 wavefronts) n = 2048 63.9 -> 70.3,
 // 4096 69.5 -> 72.8, 8192 70.6 -> 74.1.  FP32: 32x32 1: 43 -> 84, 12: 95 ->

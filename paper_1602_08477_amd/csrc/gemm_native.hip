@@ -191,10 +191,10 @@ int pick_division(int dtype, bool ring, int64_t m, int64_t n, int64_t k) {
   if (!ring) return (f64 ? best_division(kReg64, m, n, k) : best_division(kReg32, m, n, k))->cfg;
   const int cfg = (f64 ? best_division(kRing64, m, n, k) : best_division(kRing32, m, n, k))->cfg;
   // Between 2^20 and 2^22 outputs the 64x64 and 64x32 tiles run as two k
-  // groups of wavefronts where those are as fast: 64x64 tiles that leave a CU
-  // at most one (two wavefronts per SIMD instead of one: within 3 % of the
-  // one-group ring either way), 64x32 tiles from four per CU (FP64 68 against
-  // 66.5 TFLOP/s).
+  // groups of wavefronts where those are about as fast: 64x64 tiles that leave a
+  // CU at most one (two wavefronts per SIMD instead of one: within 3 % of the
+  // one-group ring either way, 5 % in FP32), 64x32 tiles from four per CU (FP64
+  // 68 against 66.5 TFLOP/s).
   const int64_t outputs = m * n;
   if (outputs >= (int64_t)1 << 20 && outputs < (int64_t)1 << 22) {
     if ((cfg == 23 || cfg == 20) && tiles_of(cfg, m, n) <= kCus) return 26;

@@ -142,7 +142,9 @@ void launch_batch(Server *S, Lane &L, int64_t batch_id) {
     const mg_problem &p = q->r.p;
     // Large problems fill the GPU on their own and run faster with the
     // single-problem work divisions than as 64x64 tiles of the grouped
-    // kernel; the choice depends only on the request's own shape.
+    // kernel; the choice depends only on the request's own shape.  They are
+    // not cut along k: whether mg_gemm cuts depends on the pool's state, and a
+    // request's result must not.
     if ((double)p.m * (double)p.n * (double)p.k >= kDirectMNK) direct.push_back(q);
     else (q->r.dtype == MG_F64 ? p64 : p32).push_back(p);
   }

@@ -39,8 +39,8 @@ bool split_refill_early(int64_t k, int64_t tiles_m, int64_t tiles_n, int64_t bat
 // Work divisions of the product kernel; cfg < 0 picks by size.
 int split_num_cfgs();
 // `latency`: one call on an otherwise idle device (the all-pairs 64x64 tile at
-// the default slice count up to n = 2048 INT8 / 1024 BF16, the pair-parallel
-// division for other slice counts below one 128x128 tile per CU); false: a
+// the default slice count, the pair-parallel division for other slice counts
+// below one 128x128 tile per CU); false: a
 // device shared with other work
 // (fused divisions only, the most throughput per FLOP).  Both give the same
 // bits.

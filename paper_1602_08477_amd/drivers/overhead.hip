@@ -160,7 +160,8 @@ void one_shape(int n, int reps, hipStream_t s, bool first) {
       raw = [&, tm, tn, k] { direct(k, dim3(tm * tn), S::THREADS, S::LDS_BYTES, g, tm, tn, s); };
     } else if (cfg == 19) {
       typedef mg::DmaShape<double, 32, 32, 2, 2, 4> S;
-      auto k = mg::gemm_dma_kernel<double, 32, 32, 2, 2, 4, false, false>;
+      auto k = g.k < S::LOOP_K ? mg::gemm_dma_kernel<double, 32, 32, 2, 2, 4, false, false, 1, 1, true>
+                               : mg::gemm_dma_kernel<double, 32, 32, 2, 2, 4, false, false>;
       CK(hipFuncSetAttribute(reinterpret_cast<const void *>(k),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS_BYTES));
       raw = [&, tm, tn, k] { direct(k, dim3(tm * tn), S::THREADS, S::LDS_BYTES, g, tm, tn, s); };
