@@ -182,10 +182,10 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s) : reg128();
     case 18:
       if (!dma_ok) return launch_one<T, 256, 128, 4, 4, 1, TA, TB>(g, ks, s);
-      // FP32 on 8 wavefronts: on 16 the transposed layouts are register bound
-      // (n = 4096 A B^T 1105 -> 1026 us, A^T B 1236 -> 1043; A B 1004 -> 1016)
-      return F64 ? launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s)
-                 : launch_dma<T, 256, 128, 2, 4, 3, TA, TB>(g, ks, s);
+      // FP32 on 8 wavefronts: on 16, A^T B spills (n = 4096 1236 -> 1043 us) and
+      // A B^T reads B^T for fewer rows at a time (1105 -> 1026; A B 1004 -> 1016)
+      if constexpr (F64) return launch_dma<T, 256, 128, 4, 4, 3, TA, TB>(g, ks, s);
+      else return launch_dma<T, 256, 128, 2, 4, 3, TA, TB>(g, ks, s);
     case 19:
       if (!dma_ok) return launch_one<T, 32, 32, 2, 2, 1, TA, TB>(g, ks, s);
       return g.k < DmaShape<T, 32, 32, 2, 2, 4>::LOOP_K
@@ -196,9 +196,10 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 21:
       if (!dma_ok) return reg128();
-      if (!F64) return launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, ks, s);
-      return many ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s)
-                  : launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, ks, s);
+      if constexpr (!F64) return launch_dma<T, 128, 128, 2, 4, 2, TA, TB, 1, 2>(g, ks, s);
+      else
+        return many ? launch_dma<T, 128, 128, 2, 4, 3, TA, TB>(g, ks, s)
+                    : launch_dma<T, 128, 128, 4, 4, 3, TA, TB>(g, ks, s);
     case 22:
       return dma_ok ? launch_dma<T, 128, 128, 2, 2, 2, TA, TB>(g, ks, s) : reg128();
     case 23:
@@ -208,13 +209,13 @@ int launch_cfg(int cfg, bool dma_ok, const GemmArgs<T> &g, const KSplit<T> &ks, 
       return dma_ok ? launch_dma<T, 64, 32, 2, 2, 3, TA, TB>(g, ks, s)
                     : launch_one<T, 64, 32, 2, 2, 1, TA, TB>(g, ks, s);
     case 25: return launch_naive<T, TA, TB>(g, s);
-    case 26:  // three stages of one k-step, three workgroups per CU, against two of
-              // two and two: FP32 n = 4096 A^T B 1268 -> 1161 us, A B^T 1202 -> 1132, A B
-              // 1145 -> 1139 (n = 1024 21.2 -> 21.6); FP64 1944 -> 1920
+    case 26:  // three stages of one k-step (FP32 three workgroups per CU) instead of
+              // two of two (two): FP32 n = 4096 A^T B 1268 -> 1161 us, A B^T 1202 ->
+              // 1132, A B 1145 -> 1139 (n = 1024 21.2 -> 21.6); FP64 1944 -> 1920
       return dma_ok ? launch_dma<T, 64, 64, 2, 2, 3, TA, TB, 2>(g, ks, s)
                     : launch_one<T, 64, 64, 2, 2, 1, TA, TB>(g, ks, s);
-    case 27:  // three stages: one workgroup per CU by its registers, so two hide
-              // less (FP64 n = 4096 2.53 -> 2.14 ms, FP32 1.20 -> 1.11)
+    case 27:  // three stages: one workgroup per CU by its registers (FP32 two), so two
+              // stages hide less (FP64 n = 4096 2.53 -> 2.14 ms, FP32 1.20 -> 1.11)
       return dma_ok ? launch_dma<T, 128, 64, 2, 2, 3, TA, TB, 2>(g, ks, s)
                     : launch_one<T, 128, 64, 2, 2, 1, TA, TB>(g, ks, s);
     case 28:

@@ -106,8 +106,8 @@ namespace {
 // on 128x128 tiles, 554 on 64x64 ones, nine on every CU).
 // `over`, for the same counts: what a tile costs besides its k, in k: filling
 // its ring and writing C while no other workgroup of its CU covers them.  The
-// FP64 128x128 ring has a CU to itself, so it wins only from k of about 1000 on
-// (8192 x 8192, against 64x64 tiles: k = 64 332 against 257 us, k = 512 1099
+// FP64 128x128 ring has a CU to itself, so it wins only from k of 800 (16 tiles
+// per CU) to 2200 (4 per CU) on (8192 x 8192, against 64x64 tiles: k = 64 332 against 257 us, k = 512 1099
 // against 1020, k = 2048 73 against 70 TFLOP/s; 4096 x 4096: k = 256 165 against
 // 139).  Fitted to 40 outputs from 32 x 32 to 8192 x 8192, k = 32 to 2048, with
 // every division timed: the pick is within 1 % of the best on average.
